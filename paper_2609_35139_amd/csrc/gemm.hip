@@ -19,7 +19,7 @@
 namespace cr {
 
 // Tile geometry: a WGM x WGN grid of waves, each owning TM x TN MFMA atoms
-// of 32x32 (bf16: v_mfma_f32_32x32x16_bf16, fp32: v_mfma_f32_32x32x2_f32),
+// of 32x32 (bf16: v_mfma_f32_32x32x16_bf16, fp32: 4 x v_mfma_f32_32x32x2_f32),
 // so the workgroup tile is (WGM*32*TM) x (WGN*32*TN).  K advances in slabs
 // of one 128-byte row per tile row; STAGES slabs live in the LDS ring.  The
 // fp32 output tile is staged through LDS over the ring, EPI_ROWS rows at a
@@ -795,17 +795,18 @@ __global__ __launch_bounds__(G::NT) void gemm_nt_kernel(const T* __restrict__ A,
     // instruction order for the scheduler: the first step's LDS reads, then
     // every step's MFMAs alternating with the next step's reads (and, spread,
     // with its share of the next slab's DMA operations)
-    constexpr int NR = G::TM + G::TN, NM = G::TM * G::TN;
+    // (counted in atoms: an fp32 atom is MFMAS instructions)
+    constexpr int NR = G::TM + G::TN, NM = G::TM * G::TN, MF = MM::MFMAS;
     constexpr int NP = NR < NM ? NR : NM;
     __builtin_amdgcn_sched_group_barrier(0x100, NR, 0);        // DS reads
 #pragma unroll
     for (int ks = 0; ks + 1 < NKS; ++ks) {
 #pragma unroll
       for (int r = 0; r < NP; ++r) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x008, MF, 0);      // MFMA
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
-      if constexpr (NM > NP) __builtin_amdgcn_sched_group_barrier(0x008, NM - NP, 0);
+      if constexpr (NM > NP) __builtin_amdgcn_sched_group_barrier(0x008, (NM - NP) * MF, 0);
       if constexpr (NR > NP) __builtin_amdgcn_sched_group_barrier(0x100, NR - NP, 0);
       // (spread: this step's share of the refill after its reads and products)
       if constexpr (SPREAD) {
@@ -818,13 +819,13 @@ __global__ __launch_bounds__(G::NT) void gemm_nt_kernel(const T* __restrict__ A,
       constexpr int LAST = G::OPS - (NKS - 1) * G::OPS / NKS;
 #pragma unroll
       for (int r = 0; r < NM; ++r) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, MF, 0);
         constexpr int DQ = LAST / NM, DR = LAST % NM;   // DMA ops per product
         if (r < DR) __builtin_amdgcn_sched_group_barrier(0x020, DQ + 1, 0);
         else if constexpr (DQ > 0) __builtin_amdgcn_sched_group_barrier(0x020, DQ, 0);
       }
     } else {
-      __builtin_amdgcn_sched_group_barrier(0x008, NM, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, NM * MF, 0);
     }
   }
   // the copies past the last slab land in the ring, which the epilogue reuses
