@@ -81,8 +81,12 @@ template <typename T>
 struct EpiBias {
   __device__ int b_row(int n) const { return n; }   // output column -> weight row
   static constexpr bool kWide = true;
-  // 64-column tiles are fine for bias epilogues (8-column segments)
-  static constexpr bool kNarrow = true;
+  // kCols: the narrowest column tile the epilogue works on (besides its
+  // min_cols); kSeg: output columns a thread owns per row; rows(M): output
+  // rows the grid has to cover
+  static constexpr int kCols = 32, kSeg = 8;
+  __device__ __host__ int rows(int M) const { return M; }
+  __host__ int min_cols() const { return 32; }
   T* out; int64_t ldo; const float* bias; const T* resid; int64_t ldr; const T* resid2;
   int64_t ldr2; int gelu;
   template <int ROWS, int COLS, int NT>
@@ -153,8 +157,12 @@ struct EpiBias {
 // tiles (each inside Q, K or V and head-aligned, d_b % 128 == 0).
 template <typename T>
 struct EpiQKV {
-  static constexpr bool kWide = false;   // head-aligned 128-column tiles
-  static constexpr bool kNarrow = false;
+  static constexpr bool kWide = false;   // head-aligned tiles inside Q, K or V
+  static constexpr int kCols = 64, kSeg = 8;
+  // the attention's last key tile reads K rows and V^T columns up to the next
+  // multiple of 64
+  __device__ __host__ int rows(int M) const { return (M + 63) / 64 * 64; }
+  __host__ int min_cols() const { return 64; }   // d_head is 32 or 64
   __device__ int b_row(int n) const { return n; }   // output column -> weight row
   T* q; T* k; T* vt; int64_t n_pad; int d_b, d_head; const float* bias;
   const float2* rope;   // (cos, sin) per token
@@ -258,7 +266,7 @@ struct EpiQKV {
 template <typename T>
 struct EpiQKVh {
   static constexpr bool kWide = true;
-  static constexpr bool kNarrow = false;
+  __device__ __host__ int rows(int M) const { return M; }   // tiles of 256 rows
   T* q; T* k; T* vt; int64_t n_pad; int d_b, d_head; const float* bias;
   const float2* rope;   // (cos, sin) per token
   __device__ int b_row(int n) const {
@@ -406,7 +414,9 @@ template <typename T>
 struct EpiExpand {
   __device__ int b_row(int n) const { return n; }   // output column -> weight row
   static constexpr bool kWide = false;
-  static constexpr bool kNarrow = false;
+  static constexpr int kCols = 64, kSeg = 8;
+  __device__ __host__ int rows(int M) const { return M; }
+  __host__ int min_cols() const { return 64; }
   T* kv; KvStrides ks; const float* bias; const float* sigma; int mode; const int* keep;
   T* kvo; KvStrides kso;   // destination when repairing out of place (kvo null: in place)
   // What the prefetch holds: the stale values of the thread's rows and a
@@ -500,7 +510,9 @@ template <typename T>
 struct EpiExpandRope {
   __device__ int b_row(int n) const { return n; }   // output column -> weight row
   static constexpr bool kWide = false;   // pair registers do not fit beside a 256x256 tile
-  static constexpr bool kNarrow = false;
+  static constexpr int kCols = 64, kSeg = 16;   // a thread owns two 8-column halves
+  __device__ __host__ int rows(int M) const { return M; }
+  __host__ int min_cols() const { return ks.head_dim <= 64 && 64 % ks.head_dim == 0 ? 64 : 128; }
   T* kv; KvStrides ks; const float* bias; const float* sigma; int mode; const int* keep;
   T* kvo; KvStrides kso;   // destination when repairing out of place (kvo null: in place)
   const float2* rope;      // [M][head_dim/2] scaled (cos, sin)
@@ -628,7 +640,7 @@ __device__ __forceinline__ void wait_slab(int ahead) {
 // panels instead of each XCD fetching every panel.
 constexpr int TILE_GROUP = 8;
 template <typename G>
-__device__ __forceinline__ void tile_of(int M, int N, int& tm, int& tn) {
+__device__ __forceinline__ void tile_of(int M, int N, int& tm, int& tn) {   // M: rows to cover
   const int gm = (M + G::BM - 1) / G::BM, gn = (N + G::BN - 1) / G::BN;
   const int total = gm * gn;
   int id = blockIdx.x;
@@ -662,7 +674,7 @@ __global__ __launch_bounds__(G::NT) void gemm_nt_kernel(const T* __restrict__ A,
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int tm, tn;
-  tile_of<G>(M, N, tm, tn);
+  tile_of<G>(epi.rows(M), N, tm, tn);
   const int m0 = tm * G::BM, n0 = tn * G::BN;
   const int kg = wave / (G::WGM * G::WGN), wv = wave % (G::WGM * G::WGN);
   const int wm = (wv / G::WGN) * G::WM, wn = (wv % G::WGN) * G::WN;
@@ -894,9 +906,169 @@ __global__ __launch_bounds__(G::NT) void gemm_nt_kernel(const T* __restrict__ A,
   }
 }
 
+// Grids of few tiles (short requests).  There the time is the serial chain of
+// one workgroup's K slabs: with every wave on a part of the tile, each 128-byte
+// slab costs about 0.23 us of barrier, LDS latency and a short product chain,
+// whatever the tile and however deep the ring (4 to 9 slabs measured alike).
+// So the waves split K instead: wave w contracts slabs w, w + NW, ... over the
+// whole BM x BN tile through an LDS ring of its own, with no barrier before
+// the fp32 partial tiles are summed in wave order, and the tiles can be small
+// enough to reach every CU.  200 x 1024 x 5120: 22.9 -> 12.1 us against 64x64
+// tiles with two K groups; 57 x 512 x 512: 4.5 -> 3.5; fp32 512 x 512 x 2560:
+// 160 (128x128 tiles) -> 17.  What bounds it then is the CU's rate of copying
+// operands into LDS (about 28 B/clk), so two-slab rings do.  Splitting K over
+// workgroups too, with fp32 partials through memory, gained nothing more.
+template <typename T, int TM_, int TN_, int NW_, int STAGES_>
+struct SkinnyTile {
+  static constexpr int TM = TM_, TN = TN_, NW = NW_, STAGES = STAGES_, NT = 64 * NW;
+  static constexpr int BM = 32 * TM, BN = 32 * TN;
+  static constexpr int BK = 128 / (int)sizeof(T), VEC = 16 / (int)sizeof(T);
+  static constexpr int A_OPS = BM / 8, B_OPS = BN / 8, OPS = A_OPS + B_OPS;   // 1 KB each
+  static constexpr int STAGE_BYTES = (BM + BN) * 128, RING = STAGES * STAGE_BYTES;
+  static constexpr int LDC = BN + 4;
+  // threads that run an epilogue whose threads own SEG columns of a row each
+  template <int SEG>
+  static constexpr int ENT = BM * BN / SEG < NT ? BM * BN / SEG : NT;
+  static constexpr size_t LDS_MAIN = (size_t)NW * RING;
+  static constexpr size_t LDS_C = (size_t)NW * BM * LDC * sizeof(float);
+  static constexpr size_t LDS = LDS_MAIN > LDS_C ? LDS_MAIN : LDS_C;
+  static_assert(OPS * (STAGES - 1) <= 63, "vmcnt range");
+  static_assert(LDS <= 160 * 1024, "LDS");
+};
+
+template <typename T, typename G, typename Epi, bool SPLIT = false>
+__global__ __launch_bounds__(G::NT) void gemm_skinny_kernel(const T* __restrict__ A, int64_t lda,
+                                                            const T* __restrict__ B, int64_t ldb,
+                                                            int M, int N, int K, Epi epi,
+                                                            ASplit<T> sp) {
+  using MM = Mma32<T>;
+  using frag = typename MM::frag;
+  __shared__ __align__(1024) char smem[G::LDS];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tm, tn;
+  tile_of<G>(epi.rows(M), N, tm, tn);
+  const int m0 = tm * G::BM, n0 = tn * G::BN;
+  // slab kt of A comes from the first matrix below kt1, else from the second
+  const int KT = K / G::BK, kt1 = SPLIT ? sp.k1 / G::BK : KT;
+  const int mine = (KT - wave + G::NW - 1) / G::NW;      // slabs of this wave
+  char* ring = smem + wave * G::RING;
+
+  // DMA sources and swizzle as in gemm_nt_kernel, the whole tile per wave
+  const char* asrc[G::A_OPS];
+  const char* asrc2[SPLIT ? G::A_OPS : 1];
+  const char* bsrc[G::B_OPS];
+#pragma unroll
+  for (int r = 0; r < G::A_OPS; ++r) {
+    const int row = r * 8 + (lane >> 3), ch = ((lane & 7) ^ swz128(row)) * 16;
+    const int64_t gm = min(m0 + row, M - 1);
+    asrc[r] = reinterpret_cast<const char*>(A + gm * lda) + ch;
+    if constexpr (SPLIT) asrc2[r] = reinterpret_cast<const char*>(sp.a2 + gm * sp.lda2) + ch;
+  }
+#pragma unroll
+  for (int r = 0; r < G::B_OPS; ++r) {
+    const int row = r * 8 + (lane >> 3), ch = ((lane & 7) ^ swz128(row)) * 16;
+    bsrc[r] = reinterpret_cast<const char*>(B + (int64_t)epi.b_row(min(n0 + row, N - 1)) * ldb) + ch;
+  }
+  auto issue = [&](int i, int stage) {
+    const int kt = wave + i * G::NW;
+    char* base = ring + stage * G::STAGE_BYTES;
+#pragma unroll
+    for (int r = 0; r < G::A_OPS; ++r) {
+      const char* a = asrc[r] + (int64_t)kt * 128;
+      if constexpr (SPLIT) {
+        if (kt >= kt1) a = asrc2[r] + (int64_t)(kt - kt1) * 128;
+      }
+      dma16(a, base + r * 1024);
+    }
+#pragma unroll
+    for (int r = 0; r < G::B_OPS; ++r)
+      dma16(bsrc[r] + (int64_t)kt * 128, base + G::BM * 128 + r * 1024);
+  };
+  f32x16 acc[G::TM][G::TN];
+#pragma unroll
+  for (int i = 0; i < G::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < G::TN; ++j) acc[i][j] = f32x16{};
+  const int fr = lane & 31, fsw = (lane & 15) >> 1;
+  constexpr int NKS = G::BK / MM::KSTEP;
+  // every iteration issues one slab (past the wave's last, a copy of it into a
+  // stage nobody reads again), so slab i has landed once STAGES - 1 later ones
+  // remain in flight; only this wave reads and refills its ring
+  if (mine > 0) {
+#pragma unroll
+    for (int st = 0; st < G::STAGES - 1; ++st) issue(min(st, mine - 1), st);
+  }
+  for (int i = 0; i < mine; ++i) {
+    // the stage refilled here held slab i - 1, whose reads fed its products
+    issue(min(i + G::STAGES - 1, mine - 1), (i + G::STAGES - 1) % G::STAGES);
+    wait_vmcnt<G::OPS * (G::STAGES - 1)>();
+    const char* as = ring + (i % G::STAGES) * G::STAGE_BYTES;
+    const char* bs = as + G::BM * 128;
+    frag af[NKS][G::TM], bf[NKS][G::TN];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      const int k = ks * MM::KSTEP + (lane >> 5) * MM::KPL;
+      const int cofs = ((k / G::VEC) ^ fsw) << 4;
+#pragma unroll
+      for (int a = 0; a < G::TM; ++a)
+        af[ks][a] = *reinterpret_cast<const frag*>(as + (a * 32 + fr) * 128 + cofs);
+#pragma unroll
+      for (int b = 0; b < G::TN; ++b)
+        bf[ks][b] = *reinterpret_cast<const frag*>(bs + (b * 32 + fr) * 128 + cofs);
+    }
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+      for (int a = 0; a < G::TM; ++a)
+#pragma unroll
+        for (int b = 0; b < G::TN; ++b) acc[a][b] = MM::mma(bf[ks][b], af[ks][a], acc[a][b]);
+  }
+  wait_vmcnt<0>();   // the copies past the last slab land in the ring
+  constexpr int ENT = G::template ENT<Epi::kSeg>;
+  typename Epi::template Pre<G::BM, G::BN, ENT> pre;
+  if (tid < ENT) epi.template prefetch<G::BM, G::BN, ENT>(pre, m0, n0, M, N);
+  __syncthreads();   // every ring idle: the partial tiles go over them
+  float* Cs = reinterpret_cast<float*>(smem);
+  float* mineC = Cs + wave * G::BM * G::LDC;
+#pragma unroll
+  for (int i = 0; i < G::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < G::TN; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4*>(mineC + (i * 32 + fr) * G::LDC + j * 32 + g * 8 + (lane >> 5) * 4) =
+            make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
+                        acc[i][j][4 * g + 3]);
+  __syncthreads();
+  // sum over the waves in wave order
+  for (int e = tid; e < G::BM * G::BN / 4; e += G::NT) {
+    float4* c = reinterpret_cast<float4*>(Cs + (e / (G::BN / 4)) * G::LDC + (e % (G::BN / 4)) * 4);
+    float4 v = *c;
+#pragma unroll
+    for (int w = 1; w < G::NW; ++w) {
+      const float4 o = c[w * (G::BM * G::LDC / 4)];
+      v = make_float4(v.x + o.x, v.y + o.y, v.z + o.z, v.w + o.w);
+    }
+    *c = v;
+  }
+  __syncthreads();
+  if (tid < ENT) epi.template run<G::BM, G::BN, G::LDC, ENT>(Cs, pre, m0, n0, M, N);
+}
+
+template <typename G>
+struct IsSkinny { static constexpr bool value = false; };
+template <typename T, int TM, int TN, int NW, int ST>
+struct IsSkinny<SkinnyTile<T, TM, TN, NW, ST>> { static constexpr bool value = true; };
+
+static inline int64_t grid_tiles(int64_t M, int64_t N, int bm, int bn) {
+  return ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+}
+
 template <typename T, typename G, typename Epi, bool SPLIT = false>
 static hipError_t launch_tiled(const T* A, int64_t lda, const T* B, int64_t ldb, int M, int N,
                                int K, const Epi& epi, hipStream_t s, ASplit<T> sp = {}) {
+  constexpr bool SKINNY = IsSkinny<G>::value;
   if (M <= 0 || N <= 0) return hipSuccess;
   // the main loop streams whole 128-byte K slabs with 16-byte copies
   if (K <= 0 || K % G::BK != 0 || lda % G::VEC != 0 || ldb % G::VEC != 0 ||
@@ -905,25 +1077,39 @@ static hipError_t launch_tiled(const T* A, int64_t lda, const T* B, int64_t ldb,
   if (SPLIT && (!sp.a2 || sp.k1 <= 0 || sp.k1 >= K || sp.k1 % G::BK != 0 ||
                 sp.lda2 % G::VEC != 0 || reinterpret_cast<uintptr_t>(sp.a2) % 16 != 0))
     return hipErrorInvalidValue;
-  const int64_t tiles = (int64_t)((N + G::BN - 1) / G::BN) * ((M + G::BM - 1) / G::BM);
+  const int64_t tiles = grid_tiles(epi.rows(M), N, G::BM, G::BN);
   if (tiles >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
   dim3 grid((unsigned)tiles);
-  CR_LAUNCH((gemm_nt_kernel<T, G, Epi, SPLIT>), grid, dim3(G::NT), 0, s, A, lda, B, ldb, M, N, K,
-            epi, sp);
+  if constexpr (SKINNY)
+    CR_LAUNCH((gemm_skinny_kernel<T, G, Epi, SPLIT>), grid, dim3(G::NT), 0, s, A, lda, B, ldb, M, N,
+              K, epi, sp);
+  else
+    CR_LAUNCH((gemm_nt_kernel<T, G, Epi, SPLIT>), grid, dim3(G::NT), 0, s, A, lda, B, ldb, M, N, K,
+              epi, sp);
   return hipGetLastError();
 }
 
-// Tile choice.  bf16 products whose 256x256 tiling fills its rounds well
-// enough (round_fill, kWideGain) take 256x256 tiles of eight waves
-// (128x64 each, two per SIMD): half the operand bytes per FLOP of a 128x128
-// tile, and one workgroup per CU with a two-slab ring of 64 KB slabs.
-// Otherwise 128x128 tiles: grids of more than one workgroup per CU use four
-// waves (64x64 each) and a two-slab ring (64 KB, two workgroups resident per
-// CU hide each other's latency); grids that fit in one pass over the 256 CUs
-// use eight waves (64x32 each, so two per SIMD) and a four-slab ring (three
-// slabs in flight cover the fetch latency).  Epi::kWide is false for
-// epilogues that need a 128-column tile or more registers than the 256x256
-// tile leaves.
+// Tile choice.  A grid that can reach every CU once takes the smallest tile
+// whose grid still fits on the 256 CUs: smaller tiles shorten each workgroup's
+// chain and fetch, and a second round costs more than it saves (measured over
+// 16 to 5,120 rows, 512 to 4,096 columns, K 512 to 5,120; us per launch):
+//   32x32, 32x64 split over K by wave (SkinnyTile): above;
+//   64x64: two K groups of four waves, from K = 2560 by wave (1,024 x 1,024 x
+//     5,120: 24.0 and 21.6; x 1,024: 6.6 and 7.0);
+//   128x64 (bf16): two K groups (1,177 x 1,024 x 5,120: 28.4 against 33.2 on
+//     64x64 and 39.2 on 128x128; 1,024 x 1,536 x 512: 5.9 against 7.4);
+//   128x128 (bf16): eight waves of 64x32 on a four-slab ring (three slabs in
+//     flight cover the fetch latency), from K = 2048 two K groups of 64x64
+//     waves, which read a third fewer fragment bytes per product (+3-4%).
+// Larger bf16 grids take 256x256 tiles of eight waves (128x64 each) if those
+// fill their rounds well enough (round_fill, kWideGain): half the operand
+// bytes per FLOP of a 128x128 tile, one workgroup per CU with a two-slab ring
+// of 64 KB slabs.  Otherwise 128x128 tiles of four waves (64x64 each) and a
+// two-slab ring (64 KB, two workgroups resident per CU hide each other's
+// latency).  Larger fp32 grids are bound by the matrix cores: 128x128 tiles if
+// their grid fills its rounds, else 64x128 (512 x 18,432 x 512: 103 and 89).
+// Epi::kWide is false for epilogues that need more registers than the 256x256
+// tile leaves; Epi::kCols and min_cols() bound the tile's width from below.
 // Fraction of the workgroup slots busy over the rounds a grid of `tiles`
 // takes on `slots` resident workgroups.
 static inline double round_fill(int64_t tiles, int64_t slots) {
@@ -938,38 +1124,36 @@ constexpr double kWideGain = 1.25;
 template <typename T, typename Epi, bool SPLIT = false>
 static hipError_t launch(const T* A, int64_t lda, const T* B, int64_t ldb, int M, int N, int K,
                          const Epi& epi, hipStream_t s, ASplit<T> sp = {}) {
-  if constexpr (sizeof(T) == 2 && Epi::kWide) {
-    const int64_t wide_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
-    const int64_t tiles128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
-    const double fill128 = tiles128 <= 256 ? round_fill(tiles128, 256) : round_fill(tiles128, 512);
-    if (kWideGain * round_fill(wide_tiles, 256) >= fill128)
-      return launch_tiled<T, GemmTile<T, 4, 2, 2, 2, 4>, Epi, SPLIT>(A, lda, B, ldb, M, N, K, epi, s,
-                                                                    sp);
+#define CR_TILED(...) return launch_tiled<T, __VA_ARGS__, Epi, SPLIT>(A, lda, B, ldb, M, N, K, epi, s, sp)
+  constexpr bool BF = sizeof(T) == 2;
+  const int rows = epi.rows(M), mc = epi.min_cols();
+  auto fits = [&](int bm, int bn) { return mc <= bn && grid_tiles(rows, N, bm, bn) <= 256; };
+  if constexpr (Epi::kCols <= 32) {
+    if (fits(32, 32)) CR_TILED(SkinnyTile<T, 1, 1, 4, 2>);
   }
-  const int64_t tiles = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
-  // Grids of at most half the CUs (short batches) take 64x64 tiles instead:
-  // four times the workgroups (two resident per CU), each with a quarter of
-  // the operand bytes per slab, on eight waves as two 4-wave K groups of
-  // 32x32 waves.
-  if constexpr (sizeof(T) == 2 && Epi::kNarrow) {
-    if (tiles <= 128)
-      return launch_tiled<T, GemmTile<T, 1, 1, 4, 2, 2, false, 2>, Epi, SPLIT>(A, lda, B, ldb, M, N,
-                                                                              K, epi, s, sp);
-  }
-  if (tiles <= 256) {
-    // long K: two 4-wave groups of 64x64 waves, each on half of every slab's
-    // k-steps, read a third fewer fragment bytes from LDS per product than
-    // eight waves of 64x32 (+3-4% at K = 2048-4096; at K = 1024 the extra
-    // partial-tile sum costs more than it saves)
-    if constexpr (sizeof(T) == 2) {
-      if (K >= 2048)
-        return launch_tiled<T, GemmTile<T, 2, 2, 4, 2, 2, false, 2>, Epi, SPLIT>(A, lda, B, ldb, M, N,
-                                                                                K, epi, s, sp);
+  if (fits(32, 64)) CR_TILED(SkinnyTile<T, 1, 2, 4, 2>);
+  if (fits(64, 64)) {
+    // (an epilogue of 16 columns per thread has no row left for eight waves)
+    if constexpr (Epi::kSeg == 8) {
+      if (!BF || K < 2560) CR_TILED(GemmTile<T, 1, 1, 4, 2, 2, false, 2>);
     }
-    return launch_tiled<T, GemmTile<T, 2, 1, 4, 2, 4>, Epi, SPLIT>(A, lda, B, ldb, M, N, K, epi, s,
-                                                                 sp);
+    CR_TILED(SkinnyTile<T, 2, 2, 4, 2>);
   }
-  return launch_tiled<T, GemmTile<T, 2, 2, 2>, Epi, SPLIT>(A, lda, B, ldb, M, N, K, epi, s, sp);
+  const int64_t tiles = grid_tiles(rows, N, 128, 128);
+  const double fill128 = round_fill(tiles, tiles <= 256 ? 256 : 512);
+  if constexpr (BF) {
+    if (fits(128, 64)) CR_TILED(GemmTile<T, 2, 1, 4, 2, 2, false, 2>);
+    if constexpr (Epi::kWide) {
+      if (kWideGain * round_fill(grid_tiles(rows, N, 256, 256), 256) >= fill128)
+        CR_TILED(GemmTile<T, 4, 2, 2, 2, 4>);
+    }
+    if (tiles <= 256 && K >= 2048) CR_TILED(GemmTile<T, 2, 2, 4, 2, 2, false, 2>);
+  } else {
+    if (fill128 < 0.9) CR_TILED(GemmTile<T, 1, 2, 2, 2, 2>);
+  }
+  if (tiles <= 256) CR_TILED(GemmTile<T, 2, 1, 4, 2, 4>);
+  CR_TILED(GemmTile<T, 2, 2, 2>);
+#undef CR_TILED
 }
 
 template <typename T>

@@ -104,6 +104,28 @@ def test_parity_small(cfg):
     assert_parity(Y, oracle_repair(inp), W.kv_layer_major_to_canonical(inp.kv), w)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [31, 256, 257, 513, 1025, 2049])
+def test_parity_at_tile_boundaries(n, dtype):
+    """Token counts around which the GEMMs change tiles (d_b = 1024: the
+    1,024-column products hold 256 tiles of 32x32 at 256 tokens, of 32x64 at
+    512, 64x64 at 1,024 and 128x64 at 2,048; the wider products change
+    earlier), K from 64 to 4,160, last tiles one row high, and keys placed so
+    that the narrow rotating output tiles run too."""
+    lengths = ((n // 3, 0, n - n // 3 - 5), (5,))
+    w = small_workload(lengths, seed=13, dtype=dtype, L=1, H=2, dh=64, E=64, d_c=64, d_b=1024,
+                       n_heads=16, d_seg=8, n_blocks=2, ffn_mult=4)
+    inp = W.make_inputs(w)
+    opts = dict(global_rope=dict(theta=1e4), position_offset=[3, 0])
+    from helpers import oracle_kwargs
+    from paper_2609_35139_amd import binding as B
+    rep = repairer_for(w, inp.weights)
+    X = W.kv_layer_major_to_canonical(inp.kv)
+    assert_parity(gpu_repair(inp, rep=rep), oracle_repair(inp), X, w)
+    assert_parity(gpu_repair(inp, rep=rep, options=B.Options(**opts)),
+                  oracle_repair(inp, **oracle_kwargs(w, **opts)), X, w)
+
+
 def test_empty_batch_is_a_no_op():
     """Requests whose chunks are all empty: nothing is launched, the call
     succeeds and the cache buffer is untouched."""
