@@ -9,8 +9,8 @@
 // loaded) and applies per-element masking only on tiles that are not fully
 // inside every row's interval.
 //
-// A workgroup owns 128 queries of one head (32 per wave; 64 queries for
-// grids too small to fill the chip, see below).  Scores are formed
+// A workgroup owns 128 queries of one head (32 per wave; 64 or 32 queries for
+// grids too small to fill the chip, see attention_d).  Scores are formed
 // transposed, S^T = K Q^T, with 32x32 MFMA atoms, so that each lane holds the
 // scores of one query: the online-softmax max and sum are register
 // reductions plus one in-register exchange with lane ^ 32.  The K rows of
@@ -38,12 +38,13 @@ namespace cr {
 // largest tile row sum accepted without re-deriving the reference max
 constexpr float kMaxTileSum = 16777216.0f;   // 2^24
 
-// Eight waves per workgroup in GROUPS = 8 / WPG groups of WPG waves: a
-// workgroup owns BQ = 32 * WPG queries, and the groups split its key tiles.
-template <typename T, int D, int STAGES_ = 4, int WPG_ = 4>
+// WAVES waves per workgroup in GROUPS = WAVES / WPG groups of WPG waves: a
+// workgroup owns BQ = 32 * WPG queries, and the groups split its key tiles of
+// BKV keys.
+template <typename T, int D, int STAGES_ = 4, int WPG_ = 4, int WAVES_ = 8, int BKV_ = 64>
 struct AttnCfg {
-  static constexpr int WPG = WPG_, BQ = 32 * WPG, BKV = 64, STAGES = STAGES_;
-  static constexpr int GROUPS = 8 / WPG, NT = 512;
+  static constexpr int WPG = WPG_, BQ = 32 * WPG, BKV = BKV_, STAGES = STAGES_, WAVES = WAVES_;
+  static constexpr int GROUPS = WAVES / WPG, NT = 64 * WAVES;
   static constexpr int VEC = 16 / (int)sizeof(T);
   static constexpr int RBK = D * (int)sizeof(T);      // K tile row bytes
   static constexpr int RBV = BKV * (int)sizeof(T);    // V^T tile row bytes
@@ -59,7 +60,7 @@ struct AttnCfg {
   static constexpr int MLD = D + 1;
   static constexpr int MERGE_ONE = BQ * MLD * 4 + 2 * BQ * 2 * 4;
   static constexpr int MERGE_BYTES = (GROUPS - 1) * MERGE_ONE;
-  static_assert(GROUPS * WPG == 8 && K_ROUNDS * WPG * 1024 == K_BYTES &&
+  static_assert(GROUPS * WPG == WAVES && BKV % 32 == 0 && K_ROUNDS * WPG * 1024 == K_BYTES &&
                 V_ROUNDS * WPG * 1024 == V_BYTES, "wave groups");
   static constexpr int LDS = GROUPS * RING_BYTES > MERGE_BYTES ? GROUPS * RING_BYTES : MERGE_BYTES;
 };
@@ -76,17 +77,17 @@ __device__ __forceinline__ int score_key(int g, int i) { return (i >> 3) * 16 + 
 // softmax state and LDS ring; group 1's partial result is merged into group
 // 0's at the end.  This halves the critical path of the long query tiles of
 // late chunks and keeps two waves per SIMD so that one wave's softmax
-// overlaps the other's MFMAs.  A grid of fewer workgroups than half the CUs
-// (a short batch) instead takes 64-query tiles with four groups of two
-// waves (tiles g, g + 4, ...; two-slot rings, merged in group order): twice
-// the workgroups, each group walking a quarter of the key tiles.
+// overlaps the other's MFMAs.  A small grid (a short batch) instead takes
+// 64- or 32-query tiles with four groups of two waves or one (tiles g, g + 4,
+// ...; two-slot rings, merged in group order): more workgroups, each group
+// walking a quarter of the key tiles.
 //
 // Q arrives pre-scaled by log2(e)/sqrt(d_head) (QKV epilogue), so scores are
 // in exp2 units.  K and V^T are padded with finite rows up to n_pad, so tile
 // loads need no clamping.  The tile loop is unrolled over the STAGES ring
 // slots: every LDS address is a per-lane base plus a compile-time offset.
-template <typename T, int D, int STAGES = 4, int WPG = 4>
-__global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
+template <typename T, int D, int STAGES = 4, int WPG = 4, int WAVES = 8, int BKV = 64>
+__global__ __launch_bounds__(64 * WAVES) void attention_kernel(const T* __restrict__ Q,
                                                         const T* __restrict__ Kg,
                                                         const T* __restrict__ Vt,
                                                         T* __restrict__ O, int N, int d_b,
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
                                                         const int* __restrict__ lo_arr,
                                                         const int* __restrict__ hi_arr,
                                                         int n_qtiles) {
-  using C = AttnCfg<T, D, STAGES, WPG>;
+  using C = AttnCfg<T, D, STAGES, WPG, WAVES, BKV>;
   using MM = Mma32<T>;
   using frag = typename MM::frag;
   using SK = Swz<C::RBK>;
@@ -103,6 +104,7 @@ __global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
   constexpr int QF = D / KSTEP;          // Q fragments per lane
   constexpr int DT = D / 32;             // 32-row tiles of O^T
   constexpr int PS = 32 / KSTEP;         // P fragments per 32-key sub-tile
+  constexpr int RT = C::BKV / 32;        // 32-key sub-tiles of a key tile
   __shared__ __align__(1024) char lds[C::LDS];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -167,9 +169,9 @@ __global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
     const int k = kk * KSTEP + g * KPL;
     kp[kk] = ring + SK::offset(krow, k / C::VEC) + (k % C::VEC) * (int)sizeof(T);
   }
-  const char* vp[2][PS];
+  const char* vp[RT][PS];
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int s2 = 0; s2 < PS; ++s2) {
       const int kofs = rt * 32 + score_key(g, s2 * KPL);
@@ -215,9 +217,9 @@ __global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
     __builtin_amdgcn_iglp_opt(0);
 
     // S^T = K Q^T for two 32-key sub-tiles; all fragment reads first
-    frag kf[2][QF];
+    frag kf[RT][QF];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
       for (int kk = 0; kk < QF; ++kk)
         kf[rt][kk] = *reinterpret_cast<const frag*>(kp[kk] + (SO + rt * 32 * C::RBK));
@@ -225,10 +227,10 @@ __global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
     // products so that their LDS latency hides behind the MFMAs and softmax
     // (bf16; the fp32 fragments are too many registers to hold that long)
     constexpr bool kEarlyV = sizeof(T) == 2;
-    frag vf[2][PS][DT];
+    frag vf[RT][PS][DT];
     auto read_v = [&] {
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
+      for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int s2 = 0; s2 < PS; ++s2)
 #pragma unroll
@@ -242,9 +244,9 @@ __global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
     issue(min(it + C::STAGES - 1, mine - 1), ((J + C::STAGES - 1) % C::STAGES) * C::STAGE_BYTES);
     // the accumulators start at -m_use, so the scores arrive already shifted
     // by the row's reference max (no per-score subtraction)
-    f32x16 s[2];
+    f32x16 s[RT];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
+    for (int rt = 0; rt < RT; ++rt) {
       s[rt] = MM::mma(kf[rt][0], qf[0], negm);
 #pragma unroll
       for (int kk = 1; kk < QF; ++kk) s[rt] = MM::mma(kf[rt][kk], qf[kk], s[rt]);
@@ -252,7 +254,7 @@ __global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
     const int k0 = kb + (C::GROUPS * it + grp) * C::BKV;
     if (!(k0 >= wmax_lo && k0 + C::BKV <= wmin_hi)) {
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
+      for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int key = k0 + rt * 32 + score_key(g, i);
@@ -261,12 +263,12 @@ __global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
     }
     // probabilities packed straight into the B operand of P V; the tile's
     // row sum is taken over the packed values the product uses
-    frag pb[2][PS];
+    frag pb[RT][PS];
     auto probs = [&](auto shifted, float shift) {
       // one partial sum per fragment, so the dot2 chains are independent
-      float tp[2][PS];
+      float tp[RT][PS];
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
+      for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int s2 = 0; s2 < PS; ++s2) {
           float pv[KPL];
@@ -279,7 +281,7 @@ __global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
         }
       float ts = 0.f;
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
+      for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int s2 = 0; s2 < PS; ++s2) ts += tp[rt][s2];
       return ts;
@@ -300,7 +302,7 @@ __global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
     if (exact) {
       float mx = -INFINITY;
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
+      for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[rt][i]);
       mx = halves_max(mx);
@@ -321,7 +323,7 @@ __global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
     lsum += ts;
     if constexpr (!kEarlyV) read_v();
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
       for (int s2 = 0; s2 < PS; ++s2)
 #pragma unroll
@@ -429,44 +431,62 @@ __global__ __launch_bounds__(512) void attention_kernel(const T* __restrict__ Q,
   }
 }
 
+template <typename T, int D, int STAGES, int WPG, int WAVES, int BKV>
+static hipError_t launch_attention(const T* q, const T* k, const T* vt, T* o, int N, int d_b,
+                                   int n_heads, int64_t n_pad, const int* lo, const int* hi,
+                                   hipStream_t s) {
+  constexpr int BQ = 32 * WPG;
+  const int n_qtiles = (N + BQ - 1) / BQ;
+  CR_LAUNCH((attention_kernel<T, D, STAGES, WPG, WAVES, BKV>), dim3(n_qtiles * n_heads),
+            dim3(64 * WAVES), 0, s, q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, n_qtiles);
+  return hipGetLastError();
+}
+
+// Query tiles.  A grid that leaves CUs idle, or has them all wait for the few
+// workgroups of the last chunks, is bound by one workgroup's walk over its key
+// tiles, so it takes shorter tiles and more key groups (16 heads of 64 unless
+// said; us):
+//   bf16, 32-query tiles with four one-wave groups while their grid fits the
+//     256 CUs (200 tokens 6.1 -> 5.5, 57 tokens x 8 heads 5.1 -> 4.9 and
+//     4 x 256 x 8 heads 9.1 -> 8.1 against the 64-query tiles);
+//   bf16, 64-query tiles with four two-wave groups while the 128-query grid is
+//     smaller than the chip (1,177 ragged tokens 21.9 -> 14.8, 2,500 tokens x
+//     8 heads 26.6 -> 20.4 against 128-query tiles; at 256 workgroups, 2,048
+//     tokens, both take 21.8);
+//   fp32, 32-query tiles with four groups and 32-key tiles (two-slot rings of
+//     16 KB per group) below two 128-query workgroups per CU (2 x 256 tokens x
+//     8 heads 37 -> 13.5, 2,048 x 8 heads 130 -> 55; at 512 workgroups, 4,096
+//     tokens, 297 against 358).
+template <typename T, int D>
+static hipError_t attention_d(const T* q, const T* k, const T* vt, T* o, int N, int d_b,
+                              int n_heads, int64_t n_pad, const int* lo, const int* hi,
+                              hipStream_t s) {
+  const int64_t wg128 = (int64_t)((N + 127) / 128) * n_heads;
+  const int64_t wg32 = (int64_t)((N + 31) / 32) * n_heads;
+  if constexpr (sizeof(T) == 2) {
+    if (wg32 <= 256)
+      return launch_attention<T, D, 2, 1, 4, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
+    if (wg128 < 256)
+      return launch_attention<T, D, 2, 2, 8, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
+    return launch_attention<T, D, 4, 4, 8, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
+  } else {
+    // (two-slot rings: two rings of 64 KB fit in 160 KB of LDS)
+    if (wg128 < 512)
+      return launch_attention<T, D, 2, 1, 4, 32>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
+    return launch_attention<T, D, 2, 4, 8, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
+  }
+}
+
 template <typename T>
 hipError_t attention(const T* q, const T* k, const T* vt, T* o, int N, int d_b, int n_heads,
                      int d_head, int64_t n_pad, const int* lo, const int* hi, hipStream_t s) {
   if (N <= 0) return hipSuccess;
   if (n_pad < ((N + 63) / 64) * 64) return hipErrorInvalidValue;
-  const int n_qtiles = (N + 127) / 128;
-  dim3 grid(n_qtiles * n_heads);
-  // two rings (one per wave group) must fit in 160 KB of LDS
-  constexpr int kStages = sizeof(T) == 2 ? 4 : 2;
-  // A grid of fewer workgroups than half the CUs (short batches) takes
-  // 64-query tiles whose four 2-wave groups split the key tiles (two-slot
-  // rings): twice the workgroups, each with half the key tiles per group.
-  if constexpr (sizeof(T) == 2) {
-    if ((int64_t)n_qtiles * n_heads < 128) {
-      const int n_q64 = (N + 63) / 64;
-      dim3 g64(n_q64 * n_heads);
-      if (d_head == 64) {
-        CR_LAUNCH((attention_kernel<T, 64, 2, 2>), g64, dim3(512), 0, s, q, k, vt, o, N, d_b,
-                  n_heads, n_pad, lo, hi, n_q64);
-        return hipGetLastError();
-      }
-      if (d_head == 32) {
-        CR_LAUNCH((attention_kernel<T, 32, 2, 2>), g64, dim3(512), 0, s, q, k, vt, o, N, d_b,
-                  n_heads, n_pad, lo, hi, n_q64);
-        return hipGetLastError();
-      }
-    }
-  }
-  if (d_head == 64) {
-    CR_LAUNCH((attention_kernel<T, 64, kStages>), grid, dim3(512), 0, s, q, k, vt, o, N, d_b,
-              n_heads, n_pad, lo, hi, n_qtiles);
-  } else if (d_head == 32) {
-    CR_LAUNCH((attention_kernel<T, 32, kStages>), grid, dim3(512), 0, s, q, k, vt, o, N, d_b,
-              n_heads, n_pad, lo, hi, n_qtiles);
-  } else {
-    return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  if (d_head == 64)
+    return attention_d<T, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
+  if (d_head == 32)
+    return attention_d<T, 32>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
+  return hipErrorInvalidValue;
 }
 
 template hipError_t attention<bf16>(const bf16*, const bf16*, const bf16*, bf16*, int, int, int,

@@ -251,3 +251,24 @@ def test_global_placement_on_128_query_tiles():
     Yr = oracle_repair(inp, global_rope=dict(inv_freq=_freqs(t.head_dim, 1e4), scale=1.0,
                                              position_offset=[5, 900]))
     assert_parity(Y, Yr, X, w)
+
+
+@pytest.mark.parametrize("name", ["block_causal", "token_causal", "bidirectional",
+                                  "block_diagonal"])
+@pytest.mark.parametrize("n,heads,d_b,dtype", [
+    (512, 16, 1024, "bf16"),     # 256 workgroups of 32-query tiles, four key groups
+    (513, 16, 1024, "bf16"),     # one more: 64-query tiles
+    (1177, 32, 2048, "bf16"),    # 320 of 128-query tiles, 64-wide heads
+    (1177, 32, 1024, "bf16"),    # the same, 32-wide heads
+    (701, 8, 512, "f32"),        # 32-query tiles and 32-key tiles
+    (2049, 32, 1024, "f32"),     # 544 of 128-query tiles
+])
+def test_attention_tilings(n, heads, d_b, dtype, name):
+    """Every query tiling of the attention, under every topology, on two
+    ragged requests whose chunks straddle query and key tiles."""
+    from paper_2609_35139_amd.binding import Options
+    a = n // 2 + 3
+    w, inp, X = _case(dict(lengths=((a // 3, 1, a - a // 3 - 1), (n - a - 70, 0, 70)),
+                           dtype=dtype, L=1, H=1, dh=64, E=64, d_c=64, d_b=d_b, n_heads=heads,
+                           d_seg=8, n_blocks=1))
+    assert_parity(gpu_repair(inp, options=Options(mask=name)), oracle_repair(inp, mask=name), X, w)
