@@ -2,8 +2,8 @@
 //
 // C[M][N] = A[M][K] * B[N][K]^T with both operands K-contiguous (activations
 // row-major, weights prepared as [out][in]).  A workgroup owns an output
-// tile (128x128 on four waves or 256x256 on eight) split in wave sub-tiles
-// computed with 32x32 MFMA atoms.
+// tile (from 32x32 to 256x256, see launch()) split in wave sub-tiles computed
+// with 32x32 MFMA atoms.
 // K advances in slabs of 128 bytes per row, fetched straight from global
 // memory into an LDS ring with global_load_lds (no register staging); rows
 // are XOR-swizzled in LDS so fragment reads are conflict-free.  The MFMA
@@ -14,6 +14,9 @@
 // epilogue then reads and writes whole 16-byte row segments (bias, GELU,
 // residual adds, RoPE, transposed V, the strided output add into the KV
 // cache with optional global placement of the keys).
+#include <algorithm>
+#include <type_traits>
+
 #include "launch.h"
 
 namespace cr {
@@ -22,19 +25,15 @@ namespace cr {
 // of 32x32 (bf16: v_mfma_f32_32x32x16_bf16, fp32: 4 x v_mfma_f32_32x32x2_f32),
 // so the workgroup tile is (WGM*32*TM) x (WGN*32*TN).  K advances in slabs
 // of one 128-byte row per tile row; STAGES slabs live in the LDS ring.  The
-// fp32 output tile is staged through LDS over the ring, EPI_ROWS rows at a
-// time (the whole tile, or half of it for 256-row tiles).
+// fp32 output tile is staged through LDS over the ring.
 template <typename T, int TM_, int TN_, int STAGES_, int WGM_ = 2, int WGN_ = 2,
-          bool EARLY2_ = false, int KS_ = 1>
+          int KS_ = 1>
 struct GemmTile {
   static constexpr int TM = TM_, TN = TN_, STAGES = STAGES_, WGM = WGM_, WGN = WGN_;
   // KS wave groups of WGM x WGN waves each take 1/KS of every slab's k-steps
   // over the whole tile; their fp32 partial tiles are summed in a fixed
   // order through LDS before the epilogue
   static constexpr int KS = KS_;
-  // two staging passes: the first pass's epilogue loads go out before the
-  // main loop too
-  static constexpr bool EARLY2 = EARLY2_;
   static constexpr int NW = WGM * WGN * KS, NT = 64 * NW;
   static constexpr int WM = 32 * TM, WN = 32 * TN;
   static constexpr int BM = WGM * WM, BN = WGN * WN;
@@ -45,16 +44,11 @@ struct GemmTile {
   static constexpr int OPS = A_ROUNDS + B_ROUNDS;
   static constexpr int STAGE_BYTES = (BM + BN) * 128;
   static constexpr int LDC = BN + 4;                // fp32 staging row (16-byte aligned rows)
-  static constexpr int EPI_ROWS = BM > 128 ? BM / 2 : BM;
-  // a single staging pass issues its epilogue loads before the main loop
-  static constexpr bool EARLY = EPI_ROWS == BM;
   static constexpr size_t LDS_MAIN = (size_t)STAGES * STAGE_BYTES;
-  static constexpr size_t LDS_C = (size_t)EPI_ROWS * LDC * sizeof(float);
+  static constexpr size_t LDS_C = (size_t)BM * LDC * sizeof(float);
   static constexpr size_t LDS = LDS_MAIN > LDS_C ? LDS_MAIN : LDS_C;
   static_assert(OPS * (STAGES - 2) <= 63, "vmcnt range");
   static_assert(A_ROUNDS * NT == BM * 8 && B_ROUNDS * NT == BN * 8, "DMA rounds");
-  static_assert(WM % EPI_ROWS == 0 || EPI_ROWS % WM == 0, "staging passes");
-  static_assert(KS == 1 || EPI_ROWS == BM, "split-K tiles stage in one pass");
 };
 
 // Epilogues see the staged tile Cs[ROWS][LDC] (fp32) whose element (r, c)
@@ -80,19 +74,20 @@ __device__ __forceinline__ void load8f(const float* p, float* v) {
 template <typename T>
 struct EpiBias {
   __device__ int b_row(int n) const { return n; }   // output column -> weight row
+  static constexpr bool kInOrder = true;
   static constexpr bool kWide = true;
   // kCols: the narrowest column tile the epilogue works on (besides its
   // min_cols); kSeg: output columns a thread owns per row; rows(M): output
   // rows the grid has to cover
   static constexpr int kCols = 32, kSeg = 8;
+  static constexpr bool kBoth = true;   // two passes' Pre records fit beside a 256x256 tile
   __device__ __host__ int rows(int M) const { return M; }
   __host__ int min_cols() const { return 32; }
-  T* out; int64_t ldo; const float* bias; const T* resid; int64_t ldr; const T* resid2;
-  int64_t ldr2; int gelu;
+  T* out; int64_t ldo; const float* bias; const T* resid; int64_t ldr; int gelu;
   template <int ROWS, int COLS, int NT>
   struct Pre {
     float b[8];
-    Vec8<T> rv[SegMap<ROWS, COLS, NT>::PASSES], rv2[SegMap<ROWS, COLS, NT>::PASSES];
+    Vec8<T> rv[SegMap<ROWS, COLS, NT>::PASSES];
   };
   template <int ROWS, int COLS, int NT>
   __device__ void prefetch(Pre<ROWS, COLS, NT>& p, int m0, int n0, int M, int N) const {
@@ -105,7 +100,6 @@ struct EpiBias {
       const int gm = m0 + S::row(q);
       if (gm >= M) continue;
       if (resid) p.rv[q].load(resid + (int64_t)gm * ldr + gn);
-      if (resid2) p.rv2[q].load(resid2 + (int64_t)gm * ldr2 + gn);
     }
   }
   template <int ROWS, int COLS, int LDC, int NT>
@@ -143,11 +137,6 @@ struct EpiBias {
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = rf[k] + v[k];
       }
-      if (resid2) {
-        float rf[8]; p.rv2[q].to_float(rf);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = v[k] + rf[k];
-      }
       Vec8<T> o; o.from_float(v); o.store(out + (int64_t)gm * ldo + gn);
     }
   }
@@ -158,12 +147,14 @@ struct EpiBias {
 template <typename T>
 struct EpiQKV {
   static constexpr bool kWide = false;   // head-aligned tiles inside Q, K or V
+  static constexpr bool kBoth = true;
   static constexpr int kCols = 64, kSeg = 8;
   // the attention's last key tile reads K rows and V^T columns up to the next
   // multiple of 64
   __device__ __host__ int rows(int M) const { return (M + 63) / 64 * 64; }
   __host__ int min_cols() const { return 64; }   // d_head is 32 or 64
   __device__ int b_row(int n) const { return n; }   // output column -> weight row
+  static constexpr bool kInOrder = true;
   T* q; T* k; T* vt; int64_t n_pad; int d_b, d_head; const float* bias;
   const float2* rope;   // (cos, sin) per token
   template <int ROWS, int COLS, int NT>
@@ -266,9 +257,11 @@ struct EpiQKV {
 template <typename T>
 struct EpiQKVh {
   static constexpr bool kWide = true;
+  static constexpr bool kBoth = false;
   __device__ __host__ int rows(int M) const { return M; }   // tiles of 256 rows
   T* q; T* k; T* vt; int64_t n_pad; int d_b, d_head; const float* bias;
   const float2* rope;   // (cos, sin) per token
+  static constexpr bool kInOrder = false;
   __device__ int b_row(int n) const {
     const int g3 = 3 * d_head, rem = n % g3;
     return (rem / d_head) * d_b + (n / g3) * d_head + rem % d_head;
@@ -413,7 +406,9 @@ __device__ __forceinline__ T* kv_coord(T* kv, const KvStrides& ks, int j, bool* 
 template <typename T>
 struct EpiExpand {
   __device__ int b_row(int n) const { return n; }   // output column -> weight row
+  static constexpr bool kInOrder = true;
   static constexpr bool kWide = false;
+  static constexpr bool kBoth = true;
   static constexpr int kCols = 64, kSeg = 8;
   __device__ __host__ int rows(int M) const { return M; }
   __host__ int min_cols() const { return 64; }
@@ -509,6 +504,7 @@ struct EpiExpand {
 template <typename T>
 struct EpiExpandRope {
   __device__ int b_row(int n) const { return n; }   // output column -> weight row
+  static constexpr bool kInOrder = true;
   static constexpr bool kWide = false;   // pair registers do not fit beside a 256x256 tile
   static constexpr int kCols = 64, kSeg = 16;   // a thread owns two 8-column halves
   __device__ __host__ int rows(int M) const { return M; }
@@ -728,8 +724,8 @@ __global__ __launch_bounds__(G::NT) void gemm_nt_kernel(const T* __restrict__ A,
 #pragma unroll
     for (int o = 0; o < G::OPS; ++o) dma_op(o, kt, stage);
   };
-  // Spread issue (the 8-wave 128-row tiles, whose 4-slab rings give a refill
-  // three iterations to land): the refill goes out in equal shares over the
+  // Spread issue (the 8-wave tiles, whose 4-slab rings give a refill three
+  // iterations to land): the refill goes out in equal shares over the
   // slab's k-steps, each share after that step's fragment reads for the next
   // step (a DMA writes LDS, so the compiler keeps it behind every earlier
   // read) and among its products, instead of as a burst after the barrier.
@@ -738,15 +734,13 @@ __global__ __launch_bounds__(G::NT) void gemm_nt_kernel(const T* __restrict__ A,
   // nobody reads again, so each iteration issues the same OPS operations and
   // waits for the same count.  (2-slab rings keep the burst: their refill
   // must land within the iteration.)
-  constexpr bool SPREAD = G::BM <= 128 && G::NW == 8;
+  constexpr bool SPREAD = G::NW == 8;
 
   // the epilogue's global loads (bias, residuals, the stale cache) go out
   // before the main loop and land while it runs
-  // (a single staging pass: before the main loop, where they land while it
-  // runs; two passes: before each pass, so the loop keeps its registers)
-  constexpr int ER = G::EPI_ROWS;
+  constexpr int ER = G::BM;
   typename Epi::template Pre<ER, G::BN, G::NT> pre;
-  if constexpr (G::EARLY || G::EARLY2) epi.template prefetch<ER, G::BN, G::NT>(pre, m0, n0, M, N);
+  epi.template prefetch<ER, G::BN, G::NT>(pre, m0, n0, M, N);
 
   f32x16 acc[G::TM][G::TN];
 #pragma unroll
@@ -846,8 +840,7 @@ __global__ __launch_bounds__(G::NT) void gemm_nt_kernel(const T* __restrict__ A,
   // Epilogue.  With the weight tile as the MFMA's first operand, lane l of
   // atom (i, j) holds output row wm + i*32 + (l & 31) and, in registers
   // 4g .. 4g+3, the consecutive columns wn + j*32 + 8g + 4*(l >> 5) + [0, 4).
-  // The tile is staged EPI_ROWS rows at a time with 16-byte LDS writes over
-  // the ring, each pass after its epilogue loads have been issued.
+  // The tile is staged with 16-byte LDS writes over the ring.
   float* Cs = reinterpret_cast<float*>(smem);
   if constexpr (G::KS == 2) {
     // group 1 stages its partial tile; group 0 adds it to its own
@@ -878,32 +871,19 @@ __global__ __launch_bounds__(G::NT) void gemm_nt_kernel(const T* __restrict__ A,
     epi.template run<ER, G::BN, G::LDC, G::NT>(Cs, pre, m0, n0, M, N);
     return;
   }
-  // the accumulator rows of staging pass `part`, written over the ring (or
-  // the previous pass's rows) once nobody reads it
-  auto stage = [&](int part) {
-    __syncthreads();
+  __syncthreads();   // ring no longer read
 #pragma unroll
-    for (int i = 0; i < G::TM; ++i) {
-      const int r0 = wm + i * 32 - part * ER;   // first row of atom row i in this pass
-      if (r0 < 0 || r0 >= ER) continue;
+  for (int i = 0; i < G::TM; ++i)
 #pragma unroll
-      for (int j = 0; j < G::TN; ++j)
+    for (int j = 0; j < G::TN; ++j)
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *reinterpret_cast<float4*>(Cs + (r0 + fr) * G::LDC + wn + j * 32 + g * 8 +
-                                     (lane >> 5) * 4) =
-              make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
-                          acc[i][j][4 * g + 3]);
-    }
-    __syncthreads();
-  };
-#pragma unroll
-  for (int part = 0; part < G::BM / ER; ++part) {
-    if (part > 0 || !(G::EARLY || G::EARLY2))
-      epi.template prefetch<ER, G::BN, G::NT>(pre, m0 + part * ER, n0, M, N);
-    stage(part);
-    epi.template run<ER, G::BN, G::LDC, G::NT>(Cs, pre, m0 + part * ER, n0, M, N);
-  }
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4*>(Cs + (wm + i * 32 + fr) * G::LDC + wn + j * 32 + g * 8 +
+                                   (lane >> 5) * 4) =
+            make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
+                        acc[i][j][4 * g + 3]);
+  __syncthreads();
+  epi.template run<ER, G::BN, G::LDC, G::NT>(Cs, pre, m0, n0, M, N);
 }
 
 // Grids of few tiles (short requests).  There the time is the serial chain of
@@ -1056,10 +1036,243 @@ __global__ __launch_bounds__(G::NT) void gemm_skinny_kernel(const T* __restrict_
   if (tid < ENT) epi.template run<G::BM, G::BN, G::LDC, ENT>(Cs, pre, m0, n0, M, N);
 }
 
+// Large grids: 256-row tiles on eight waves in two groups of four, one wave of
+// each group per SIMD, that take turns between a memory phase (LDS fragment
+// reads, DMA issue) and a matrix phase, half a phase pair apart: while one
+// wave of a SIMD issues products, the other fills its registers, so neither
+// the LDS latency nor the DMA issue (a wave is held while the CU's address
+// unit is busy) leaves the matrix cores idle.  A slab takes two phase pairs
+// per group: the upper half of the tile's rows against every column, then the
+// lower half (whose B fragments are still in registers).  The loop runs at the
+// card's power limit: 1.40 PFLOP/s by the slope over K at 4,096 x 4,096 with
+// this schedule and with all eight waves in phase alike, but this one also
+// holds it beside cold operands (31,503 x 1,024 x 5,120: 304 -> 285 us).  What
+// is left at K = 1,024 is the epilogue, 9 us of a 37 us GELU tile, in which
+// nothing overlaps (one workgroup per CU): so both staging passes' loads go out
+// at once when the loop ends (output add at 5,120 x 65,536: 826 -> 753 us) and
+// every wave takes part in both.  Writing from the accumulators without
+// staging, 16 bytes per lane and 32 per row, was slower (973 us).
+template <typename T, int TM_, int TN_, int WGM_, int WGN_>
+struct PhaseTile {
+  static constexpr int TM = TM_, TN = TN_, WGM = WGM_, WGN = WGN_;
+  static constexpr int NW = 8, NT = 512;
+  static constexpr int BM = WGM * 32 * TM, WN = 32 * TN, BN = WGN * WN;
+  static constexpr int BK = 128 / (int)sizeof(T), VEC = 16 / (int)sizeof(T);
+  static constexpr int HM = BM / 2, HTM = TM / 2;      // rows and atom rows of a half
+  static constexpr int A_OPS = HM * 8 / NT;            // DMA ops per thread: one A half,
+  static constexpr int B_OPS = BN * 8 / NT;            // B,
+  static constexpr int B0_OPS = (B_OPS + 1) / 2, B1_OPS = B_OPS - B0_OPS;   // its two parts
+  static constexpr int STAGE_BYTES = (BM + BN) * 128;
+  static constexpr int LDC = BN + 4;
+  static constexpr size_t LDS_MAIN = 2 * (size_t)STAGE_BYTES;
+  static constexpr size_t LDS_C = (size_t)HM * LDC * sizeof(float);
+  static constexpr size_t LDS = LDS_MAIN > LDS_C ? LDS_MAIN : LDS_C;
+  static_assert(WGM * WGN == NW && TM % 2 == 0 && A_OPS * NT == HM * 8 && B_OPS * NT == BN * 8,
+                "phase tile");
+};
+
+template <typename T, typename G, typename Epi, bool SPLIT = false>
+__global__ __launch_bounds__(G::NT) void gemm_phase_kernel(const T* __restrict__ A, int64_t lda,
+                                                           const T* __restrict__ B, int64_t ldb,
+                                                           int M, int N, int K, Epi epi,
+                                                           ASplit<T> sp) {
+  using MM = Mma32<T>;
+  using frag = typename MM::frag;
+  __shared__ __align__(1024) char smem[G::LDS];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wave >> 2;      // waves w and w + 4 share a SIMD
+  int tm, tn;
+  tile_of<G>(epi.rows(M), N, tm, tn);
+  const int m0 = tm * G::BM, n0 = tn * G::BN;
+  const int wr = wave / G::WGN, wc = wave % G::WGN;
+
+  // DMA sources as a uniform base, advanced by the slab, and a 32-bit offset
+  // per lane: operation r of an A half or of B fills 1 KB = rows
+  // (r * 8 + wave) * 8 + [0, 8); rows past M / N are clamped to the last one
+  const int dr = wave * 8 + (lane >> 3);
+  const char* ab = reinterpret_cast<const char*>(A + (int64_t)m0 * lda);
+  const char* ab2 = SPLIT ? reinterpret_cast<const char*>(sp.a2 + (int64_t)m0 * sp.lda2) : nullptr;
+  const char* bb = reinterpret_cast<const char*>(B + (int64_t)(Epi::kInOrder ? n0 : 0) * ldb);
+  unsigned ao[2][G::A_OPS], ao2[2][SPLIT ? G::A_OPS : 1], bo[G::B_OPS];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int r = 0; r < G::A_OPS; ++r) {
+      const int row = h * G::HM + r * 64 + dr, ch = ((lane & 7) ^ swz128(row)) * 16;
+      const int cr = min(row, M - 1 - m0);
+      ao[h][r] = (unsigned)(cr * (int)(lda * sizeof(T)) + ch);
+      if constexpr (SPLIT) ao2[h][r] = (unsigned)(cr * (int)(sp.lda2 * sizeof(T)) + ch);
+    }
+#pragma unroll
+  for (int r = 0; r < G::B_OPS; ++r) {
+    const int row = r * 64 + dr, ch = ((lane & 7) ^ swz128(row)) * 16;
+    const int br = epi.b_row(min(n0 + row, N - 1)) - (Epi::kInOrder ? n0 : 0);
+    bo[r] = (unsigned)(br * (int)(ldb * sizeof(T)) + ch);
+  }
+  const int KT = K / G::BK, kt1 = SPLIT ? sp.k1 / G::BK : KT;
+  // half h of A of slab kt; the first or second part of B
+  auto dma_a = [&](int kt, int h) {
+    char* st = smem + (kt & 1) * G::STAGE_BYTES + h * G::HM * 128 + wave * 1024;
+    const bool second = SPLIT && kt >= kt1;
+    const char* base = second ? ab2 + (int64_t)(kt - kt1) * 128 : ab + (int64_t)kt * 128;
+#pragma unroll
+    for (int r = 0; r < G::A_OPS; ++r)
+      dma16(base + (SPLIT ? (second ? ao2[h][r] : ao[h][r]) : ao[h][r]), st + r * 8192);
+  };
+  auto dma_b = [&](int kt, auto first) {
+    constexpr int r0 = decltype(first)::value ? 0 : G::B0_OPS;
+    constexpr int r1 = decltype(first)::value ? G::B0_OPS : G::B_OPS;
+    char* st = smem + (kt & 1) * G::STAGE_BYTES + G::BM * 128 + wave * 1024;
+    const char* base = bb + (int64_t)kt * 128;
+#pragma unroll
+    for (int r = r0; r < r1; ++r) dma16(base + bo[r], st + r * 8192);
+  };
+  using B0 = std::true_type;
+  using B1 = std::false_type;
+
+  constexpr int ER = G::HM;
+  f32x16 acc[G::TM][G::TN];
+#pragma unroll
+  for (int i = 0; i < G::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < G::TN; ++j) acc[i][j] = f32x16{};
+
+  const int fr = lane & 31, fsw = (lane & 15) >> 1;
+  constexpr int NKS = G::BK / MM::KSTEP;
+  frag af[NKS][G::HTM], bf[NKS][G::TN];
+  auto read_a = [&](int kt, int h) {
+    const char* as = smem + (kt & 1) * G::STAGE_BYTES + (h * G::HM + wr * 32 * G::HTM + fr) * 128;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+      for (int i = 0; i < G::HTM; ++i)
+        af[ks][i] = *reinterpret_cast<const frag*>(as + i * 4096 + (((2 * ks + (lane >> 5)) ^ fsw) << 4));
+  };
+  auto read_b = [&](int kt) {
+    const char* bs = smem + (kt & 1) * G::STAGE_BYTES + (G::BM + wc * G::WN + fr) * 128;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+      for (int j = 0; j < G::TN; ++j)
+        bf[ks][j] = *reinterpret_cast<const frag*>(bs + j * 4096 + (((2 * ks + (lane >> 5)) ^ fsw) << 4));
+  };
+  auto products = [&](auto half) {
+    constexpr int I0 = decltype(half)::value * G::HTM;
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+      for (int i = 0; i < G::HTM; ++i)
+#pragma unroll
+        for (int j = 0; j < G::TN; ++j)
+          acc[I0 + i][j] = MM::mma(bf[ks][j], af[ks][i], acc[I0 + i][j]);
+    __builtin_amdgcn_s_setprio(0);
+  };
+  auto phase_end = [&] {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Loads are issued at least three phases before their first read: B's second
+  // part and A's lower half of slab t + 1 in the upper memory phase of slab t,
+  // A's upper half and B's first part of slab t + 2 in its lower memory phase,
+  // each into a part of the ring that both groups have read (a group's reads
+  // are complete before the barrier that ends its memory phase).  Before the
+  // barrier ahead of group 0's reads every wave waits for its own operations:
+  // group 0 then ends a matrix phase, group 1 a memory phase; group 1 reads
+  // the same part a phase later.
+  constexpr int LOWER = G::A_OPS + G::B0_OPS;          // issued in a lower memory phase
+  constexpr int UPPER = G::A_OPS + G::B1_OPS;          // and in an upper one
+  dma_a(0, 0); dma_b(0, B0{});
+  dma_b(0, B1{}); dma_a(0, 1);
+  if (KT > 1) {
+    dma_a(1, 0); dma_b(1, B0{});
+    wait_vmcnt<G::A_OPS + LOWER>();
+  } else {
+    wait_vmcnt<0>();
+  }
+  phase_end();
+  if (grp == 1) phase_end();
+  // LEFT: slabs after this one, at most 2 (the ring's last loads are peeled)
+  auto slab = [&](int t, auto left) {
+    constexpr int LEFT = decltype(left)::value;
+    auto end_memory = [&](auto in_flight) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (grp == 1) wait_vmcnt<decltype(in_flight)::value>();
+      phase_end();
+    };
+    auto end_products = [&](auto in_flight) {
+      if (grp == 0) wait_vmcnt<decltype(in_flight)::value>();
+      phase_end();
+    };
+    // (A's lower half has landed)
+    using WAIT_UP = std::integral_constant<int, LEFT >= 1 ? LOWER + UPPER : 0>;
+    // (all of slab t + 1 but A's lower half)
+    using WAIT_LO = std::integral_constant<int, LEFT >= 2 ? G::A_OPS + LOWER : LEFT == 1 ? G::A_OPS : 0>;
+    read_a(t, 0);
+    read_b(t);
+    if constexpr (LEFT >= 1) {
+      dma_b(t + 1, B1{});
+      dma_a(t + 1, 1);
+    }
+    end_memory(WAIT_UP{});
+    products(std::integral_constant<int, 0>{});
+    end_products(WAIT_UP{});
+    read_a(t, 1);
+    if constexpr (LEFT >= 2) {
+      dma_a(t + 2, 0);
+      dma_b(t + 2, B0{});
+    }
+    end_memory(WAIT_LO{});
+    products(std::integral_constant<int, 1>{});
+    end_products(WAIT_LO{});
+  };
+  for (int t = 0; t + 2 < KT; ++t) slab(t, std::integral_constant<int, 2>{});
+  if (KT > 1) slab(KT - 2, std::integral_constant<int, 1>{});
+  slab(KT - 1, std::integral_constant<int, 0>{});
+  if (grp == 0) phase_end();
+
+  // Epilogue: a staging pass per half, to which every wave contributes.  The
+  // loads of both passes are issued together, into the registers that the
+  // fragments held, if the epilogue's record is small enough for that.
+  float* Cs = reinterpret_cast<float*>(smem);
+  constexpr bool BOTH = Epi::kBoth;
+  typename Epi::template Pre<ER, G::BN, G::NT> pre[BOTH ? 2 : 1];
+  if constexpr (BOTH)
+#pragma unroll
+    for (int part = 0; part < 2; ++part)
+      epi.template prefetch<ER, G::BN, G::NT>(pre[part], m0 + part * ER, n0, M, N);
+#pragma unroll
+  for (int part = 0; part < 2; ++part) {
+    if constexpr (!BOTH)
+      epi.template prefetch<ER, G::BN, G::NT>(pre[0], m0 + part * ER, n0, M, N);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < G::HTM; ++i)
+#pragma unroll
+      for (int j = 0; j < G::TN; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x16& c = acc[part * G::HTM + i][j];
+          *reinterpret_cast<float4*>(Cs + (wr * 32 * G::HTM + i * 32 + fr) * G::LDC + wc * G::WN +
+                                     j * 32 + g * 8 + (lane >> 5) * 4) =
+              make_float4(c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]);
+        }
+    __syncthreads();
+    epi.template run<ER, G::BN, G::LDC, G::NT>(Cs, pre[BOTH ? part : 0], m0 + part * ER, n0, M, N);
+  }
+}
+
 template <typename G>
 struct IsSkinny { static constexpr bool value = false; };
 template <typename T, int TM, int TN, int NW, int ST>
 struct IsSkinny<SkinnyTile<T, TM, TN, NW, ST>> { static constexpr bool value = true; };
+
+template <typename G>
+struct IsPhase { static constexpr bool value = false; };
+template <typename T, int TM, int TN, int WM, int WN>
+struct IsPhase<PhaseTile<T, TM, TN, WM, WN>> { static constexpr bool value = true; };
 
 static inline int64_t grid_tiles(int64_t M, int64_t N, int bm, int bn) {
   return ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
@@ -1083,6 +1296,9 @@ static hipError_t launch_tiled(const T* A, int64_t lda, const T* B, int64_t ldb,
   if constexpr (SKINNY)
     CR_LAUNCH((gemm_skinny_kernel<T, G, Epi, SPLIT>), grid, dim3(G::NT), 0, s, A, lda, B, ldb, M, N,
               K, epi, sp);
+  else if constexpr (IsPhase<G>::value)
+    CR_LAUNCH((gemm_phase_kernel<T, G, Epi, SPLIT>), grid, dim3(G::NT), 0, s, A, lda, B, ldb, M, N,
+              K, epi, sp);
   else
     CR_LAUNCH((gemm_nt_kernel<T, G, Epi, SPLIT>), grid, dim3(G::NT), 0, s, A, lda, B, ldb, M, N, K,
               epi, sp);
@@ -1101,15 +1317,13 @@ static hipError_t launch_tiled(const T* A, int64_t lda, const T* B, int64_t ldb,
 //   128x128 (bf16): eight waves of 64x32 on a four-slab ring (three slabs in
 //     flight cover the fetch latency), from K = 2048 two K groups of 64x64
 //     waves, which read a third fewer fragment bytes per product (+3-4%).
-// Larger bf16 grids take 256x256 tiles of eight waves (128x64 each) if those
-// fill their rounds well enough (round_fill, kWideGain): half the operand
-// bytes per FLOP of a 128x128 tile, one workgroup per CU with a two-slab ring
-// of 64 KB slabs.  Otherwise 128x128 tiles of four waves (64x64 each) and a
+// Larger bf16 grids take 256x256 tiles (PhaseTile) if those fill their rounds
+// well enough (round_fill, kWideGain): half the operand bytes per FLOP of a
+// 128x128 tile, one workgroup per CU with a two-slab ring of 64 KB slabs.  Otherwise 128x128 tiles of four waves (64x64 each) and a
 // two-slab ring (64 KB, two workgroups resident per CU hide each other's
 // latency).  Larger fp32 grids are bound by the matrix cores: 128x128 tiles if
 // their grid fills its rounds, else 64x128 (512 x 18,432 x 512: 103 and 89).
-// Epi::kWide is false for epilogues that need more registers than the 256x256
-// tile leaves; Epi::kCols and min_cols() bound the tile's width from below.
+// Epi::kWide is false for epilogues that launch() gives no 256x256 tile; Epi::kCols and min_cols() bound the tile's width from below.
 // Fraction of the workgroup slots busy over the rounds a grid of `tiles`
 // takes on `slots` resident workgroups.
 static inline double round_fill(int64_t tiles, int64_t slots) {
@@ -1135,19 +1349,19 @@ static hipError_t launch(const T* A, int64_t lda, const T* B, int64_t ldb, int M
   if (fits(64, 64)) {
     // (an epilogue of 16 columns per thread has no row left for eight waves)
     if constexpr (Epi::kSeg == 8) {
-      if (!BF || K < 2560) CR_TILED(GemmTile<T, 1, 1, 4, 2, 2, false, 2>);
+      if (!BF || K < 2560) CR_TILED(GemmTile<T, 1, 1, 4, 2, 2, 2>);
     }
     CR_TILED(SkinnyTile<T, 2, 2, 4, 2>);
   }
   const int64_t tiles = grid_tiles(rows, N, 128, 128);
   const double fill128 = round_fill(tiles, tiles <= 256 ? 256 : 512);
   if constexpr (BF) {
-    if (fits(128, 64)) CR_TILED(GemmTile<T, 2, 1, 4, 2, 2, false, 2>);
+    if (fits(128, 64)) CR_TILED(GemmTile<T, 2, 1, 4, 2, 2, 2>);
     if constexpr (Epi::kWide) {
       if (kWideGain * round_fill(grid_tiles(rows, N, 256, 256), 256) >= fill128)
-        CR_TILED(GemmTile<T, 4, 2, 2, 2, 4>);
+        CR_TILED(PhaseTile<T, 4, 2, 2, 4>);
     }
-    if (tiles <= 256 && K >= 2048) CR_TILED(GemmTile<T, 2, 2, 4, 2, 2, false, 2>);
+    if (tiles <= 256 && K >= 2048) CR_TILED(GemmTile<T, 2, 2, 4, 2, 2, 2>);
   } else {
     if (fill128 < 0.9) CR_TILED(GemmTile<T, 1, 2, 2, 2, 2>);
   }
@@ -1159,8 +1373,8 @@ static hipError_t launch(const T* A, int64_t lda, const T* B, int64_t ldb, int M
 template <typename T>
 hipError_t gemm_bias(const T* A, int64_t lda, const T* B, int64_t ldb, int M, int N, int K,
                      T* out, int64_t ldo, const float* bias, const T* resid, int64_t ldr,
-                     bool gelu, hipStream_t s, const T* resid2, int64_t ldr2) {
-  EpiBias<T> e{out, ldo, bias, resid, ldr, resid2, ldr2, gelu ? 1 : 0};
+                     bool gelu, hipStream_t s) {
+  EpiBias<T> e{out, ldo, bias, resid, ldr, gelu ? 1 : 0};
   return launch<T>(A, lda, B, ldb, M, N, K, e, s);
 }
 
@@ -1168,7 +1382,7 @@ template <typename T>
 hipError_t gemm_bias_split(const T* A, int64_t lda, int K1, const T* A2, int64_t lda2, const T* B,
                            int64_t ldb, int M, int N, int K, T* out, int64_t ldo,
                            const float* bias, const T* resid, int64_t ldr, hipStream_t s) {
-  EpiBias<T> e{out, ldo, bias, resid, ldr, nullptr, 0, 0};
+  EpiBias<T> e{out, ldo, bias, resid, ldr, 0};
   return launch<T, EpiBias<T>, true>(A, lda, B, ldb, M, N, K, e, s, ASplit<T>{A2, lda2, K1});
 }
 
@@ -1177,18 +1391,27 @@ hipError_t gemm_qkv(const T* A, int64_t lda, const T* B, int M, int K, int d_b, 
                     T* q, T* k, T* vt, int64_t n_pad, const float* bias, const float2* rope,
                     hipStream_t s) {
   const int N = 3 * d_b;
-  // 192-column tiles of whole heads on a 256x192 grid (eight waves of 64x96)
-  // when it fills its rounds well enough; otherwise 128x128 tiles in the
-  // weights' own column order.  Either grid covers rows up to roundup(M, 128)
-  // >= n_pad, so the transposed V padding is written too (A rows >= M are
-  // clamped copies: finite).
+  // Large bf16 grids: 256x192 tiles of whole heads, or 256x256 tiles in the
+  // weights' own column order (each inside Q, K or V), whichever fills its
+  // rounds better (the wider ones at a near tie: fewer operand bytes), if that
+  // beats 128x128 tiles as in launch().  d_b = 1024: 5,120 tokens, 320 tiles of
+  // 192 columns or 240 of 256, 46.2 us on 128x128 tiles and 42.2 on 256x256;
+  // 31,503 tokens 245 on 192 columns and 241 on 256.  Either grid covers rows
+  // up to roundup(M, 256) >= n_pad, so the K and transposed V padding is
+  // written too (A rows >= M are clamped copies: finite).
   if constexpr (sizeof(T) == 2) {
-    const int64_t wide = (int64_t)((M + 255) / 256) * (N / 192);
-    const int64_t tiles128 = (int64_t)((M + 127) / 128) * (N / 128);
-    const double fill128 = tiles128 <= 256 ? round_fill(tiles128, 256) : round_fill(tiles128, 512);
-    if (192 % (3 * d_head) == 0 && N % 192 == 0 && kWideGain * round_fill(wide, 256) >= fill128) {
-      EpiQKVh<T> e{q, k, vt, n_pad, d_b, d_head, bias, rope};
-      return launch_tiled<T, GemmTile<T, 2, 3, 2, 4, 2>>(A, lda, B, K, M, N, K, e, s);
+    const double heads = 192 % (3 * d_head) == 0 && N % 192 == 0
+                             ? round_fill(grid_tiles(M, N, 256, 192), 256) : 0.0;
+    const double wide = d_b % 256 == 0 ? round_fill(grid_tiles(M, N, 256, 256), 256) : 0.0;
+    const int64_t tiles128 = grid_tiles(M, N, 128, 128);
+    const double fill128 = round_fill(tiles128, tiles128 <= 256 ? 256 : 512);
+    if (kWideGain * std::max(heads, wide) >= fill128) {
+      if (heads > 1.05 * wide) {
+        EpiQKVh<T> e{q, k, vt, n_pad, d_b, d_head, bias, rope};
+        return launch_tiled<T, PhaseTile<T, 2, 3, 4, 2>>(A, lda, B, K, M, N, K, e, s);
+      }
+      EpiQKV<T> e{q, k, vt, n_pad, d_b, d_head, bias, rope};
+      return launch_tiled<T, PhaseTile<T, 4, 2, 2, 4>>(A, lda, B, K, M, N, K, e, s);
     }
   }
   EpiQKV<T> e{q, k, vt, n_pad, d_b, d_head, bias, rope};
@@ -1218,22 +1441,17 @@ hipError_t gemm_expand(const T* A, int64_t lda, const T* B, int M, int N, int K,
   }
   EpiExpand<T> e{kv, ks, bias, sigma, mode, keep, kv_out, ks_out};
   if constexpr (sizeof(T) == 2) {
-    const int64_t wide = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
-    const int64_t tiles128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
-    const double fill128 = tiles128 <= 256 ? round_fill(tiles128, 256) : round_fill(tiles128, 512);
-    // the expansion's epilogue (the stale-cache read-modify-write) gains less
-    // from the wide tile than the bias epilogues: about 5% at equal fill
-    constexpr double kExpandWideGain = 1.05;
-    if (kExpandWideGain * round_fill(wide, 256) >= fill128)
-      return launch_tiled<T, GemmTile<T, 4, 2, 2, 2, 4, true>>(A, lda, B, K, M, N, K, e, s);
+    const int64_t wide = grid_tiles(M, N, 256, 256), tiles128 = grid_tiles(M, N, 128, 128);
+    const double fill128 = round_fill(tiles128, tiles128 <= 256 ? 256 : 512);
+    if (kWideGain * round_fill(wide, 256) >= fill128)
+      return launch_tiled<T, PhaseTile<T, 4, 2, 2, 4>>(A, lda, B, K, M, N, K, e, s);
   }
   return launch<T>(A, lda, B, K, M, N, K, e, s);
 }
 
 #define CR_INST(T)                                                                              \
   template hipError_t gemm_bias<T>(const T*, int64_t, const T*, int64_t, int, int, int, T*,    \
-                                   int64_t, const float*, const T*, int64_t, bool, hipStream_t, \
-                                   const T*, int64_t);                                          \
+                                   int64_t, const float*, const T*, int64_t, bool, hipStream_t); \
   template hipError_t gemm_bias_split<T>(const T*, int64_t, int, const T*, int64_t, const T*,   \
                                          int64_t, int, int, int, T*, int64_t, const float*,      \
                                          const T*, int64_t, hipStream_t);                        \

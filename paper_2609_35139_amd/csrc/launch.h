@@ -47,11 +47,11 @@ struct KvStrides {
 hipError_t copy_table(const int32_t* host, int n, int* dev, hipStream_t s);
 
 // ---- GEMM: C[M][N] = A[M][K] * B[N][K]^T, fp32 accumulation, K % 64 == 0.
-// Bias / GELU / residual epilogue: out = (resid +) act(acc + bias) (+ resid2).
+// Bias / GELU / residual epilogue: out = (resid +) act(acc + bias).
 template <typename T>
 hipError_t gemm_bias(const T* A, int64_t lda, const T* B, int64_t ldb, int M, int N, int K,
                      T* out, int64_t ldo, const float* bias, const T* resid, int64_t ldr,
-                     bool gelu, hipStream_t s, const T* resid2 = nullptr, int64_t ldr2 = 0);
+                     bool gelu, hipStream_t s);
 
 // The same with A split along K: C = [A | A2] B^T + bias (+ resid), A
 // supplying columns [0, K1) and A2 columns [K1, K); K1 % 64 == 0.

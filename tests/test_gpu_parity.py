@@ -126,6 +126,25 @@ def test_parity_at_tile_boundaries(n, dtype):
                   oracle_repair(inp, **oracle_kwargs(w, **opts)), X, w)
 
 
+@pytest.mark.parametrize("n,cfg", [
+    # d_b = 1024: FFN1 and QKV on one round of 256x256 and 256x192 tiles, the
+    # last tile rows ragged
+    (3900, dict()),
+    # QKV on 256x256 tiles in the weights' column order
+    (4800, dict()),
+    # the output add on 256x256 tiles with the shortest K (two slabs), rows ragged
+    (1000, dict(L=8, H=8, dh=128, d_b=128, n_heads=2)),
+    # ... and four slabs, into columns that are no multiple of the tile
+    (1000, dict(L=11, H=5, dh=96, d_c=64, d_b=256, n_heads=4)),
+])
+def test_parity_on_large_tiles(n, cfg):
+    base = dict(dtype="bf16", L=1, H=2, dh=64, E=64, d_c=64, d_b=1024, n_heads=16, d_seg=8,
+                n_blocks=1, ffn_mult=4)
+    w = small_workload(((n // 4, n // 2), (n - n // 4 - n // 2 - 1, 1)), seed=19, **{**base, **cfg})
+    inp = W.make_inputs(w)
+    assert_parity(gpu_repair(inp), oracle_repair(inp), W.kv_layer_major_to_canonical(inp.kv), w)
+
+
 def test_empty_batch_is_a_no_op():
     """Requests whose chunks are all empty: nothing is launched, the call
     succeeds and the cache buffer is untouched."""
