@@ -563,7 +563,7 @@ struct EpiExpandRope {
     const int half = ks.head_dim / 2;
     constexpr int P = Pre<ROWS, COLS, NT>::P;
     const bool res = mode & EXPAND_RESIDUAL;
-    constexpr int GRP = P >= 2 ? 2 : P;             // passes whose (cos, sin) load together
+    constexpr int GRP = P % 2 == 0 ? 2 : 1;         // passes whose (cos, sin) load together
 #pragma unroll
     for (int q0 = 0; q0 < P; q0 += GRP) {
     float4 cs[GRP][4];
@@ -724,8 +724,8 @@ __global__ __launch_bounds__(G::NT) void gemm_nt_kernel(const T* __restrict__ A,
 #pragma unroll
     for (int o = 0; o < G::OPS; ++o) dma_op(o, kt, stage);
   };
-  // Spread issue (the 8-wave tiles, whose 4-slab rings give a refill three
-  // iterations to land): the refill goes out in equal shares over the
+  // Spread issue (the 8-wave tiles, whose 3- and 4-slab rings give a refill
+  // two or three iterations to land): the refill goes out in equal shares over the
   // slab's k-steps, each share after that step's fragment reads for the next
   // step (a DMA writes LDS, so the compiler keeps it behind every earlier
   // read) and among its products, instead of as a burst after the barrier.
@@ -1317,6 +1317,11 @@ static hipError_t launch_tiled(const T* A, int64_t lda, const T* B, int64_t ldb,
 //   128x128 (bf16): eight waves of 64x32 on a four-slab ring (three slabs in
 //     flight cover the fetch latency), from K = 2048 two K groups of 64x64
 //     waves, which read a third fewer fragment bytes per product (+3-4%).
+//   192x128 (bf16): eight waves of 96x32 (5,120 x 1,024 x 5,120: 74.7 -> 59.9
+//     against 128x128 tiles in two rounds, x 1,024: 19.1 -> 17.0; 1,177 x
+//     4,096 x 1,024: 19.7 -> 16.5);
+//   256x128 (bf16): two K groups, from K = 2048 (8,192 x 1,024 x 5,120: 95.1
+//     -> 82.4; x 1,024: 23.0 and 23.4).
 // Larger bf16 grids take 256x256 tiles (PhaseTile) if those fill their rounds
 // well enough (round_fill, kWideGain): half the operand bytes per FLOP of a
 // 128x128 tile, one workgroup per CU with a two-slab ring of 64 KB slabs.  Otherwise 128x128 tiles of four waves (64x64 each) and a
@@ -1357,6 +1362,10 @@ static hipError_t launch(const T* A, int64_t lda, const T* B, int64_t ldb, int M
   const double fill128 = round_fill(tiles, tiles <= 256 ? 256 : 512);
   if constexpr (BF) {
     if (fits(128, 64)) CR_TILED(GemmTile<T, 2, 1, 4, 2, 2, 2>);
+    if (tiles > 256 && fits(192, 128)) CR_TILED(GemmTile<T, 3, 1, 4, 2, 4>);
+    if constexpr (Epi::kSeg == 8) {
+      if (tiles > 256 && fits(256, 128) && K >= 2048) CR_TILED(GemmTile<T, 4, 2, 3, 2, 2, 2>);
+    }
     if constexpr (Epi::kWide) {
       if (kWideGain * round_fill(grid_tiles(rows, N, 256, 256), 256) >= fill128)
         CR_TILED(PhaseTile<T, 4, 2, 2, 4>);

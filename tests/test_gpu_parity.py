@@ -130,8 +130,12 @@ def test_parity_at_tile_boundaries(n, dtype):
     # d_b = 1024: FFN1 and QKV on one round of 256x256 and 256x192 tiles, the
     # last tile rows ragged
     (3900, dict()),
+    # 1,024-column products on 192x128 tiles; QKV on 128x128 ones
+    (4300, dict()),
     # QKV on 256x256 tiles in the weights' column order
     (4800, dict()),
+    # FFN2 and the fusion on 256x128 tiles of two K groups
+    (6200, dict(E=2048)),
     # the output add on 256x256 tiles with the shortest K (two slabs), rows ragged
     (1000, dict(L=8, H=8, dh=128, d_b=128, n_heads=2)),
     # ... and four slabs, into columns that are no multiple of the tile
