@@ -16,7 +16,7 @@ hipError_t key_rope_table(float2*, const int*, int, const KeyRope&, hipStream_t)
 
 template <typename T>
 hipError_t gemm_bias(const T*, int64_t, const T*, int64_t, int, int, int, T*, int64_t,
-                     const float*, const T*, int64_t, bool, hipStream_t, const T*, int64_t) {
+                     const float*, const T*, int64_t, bool, hipStream_t) {
   return hipErrorInvalidValue;
 }
 template <typename T>
@@ -74,8 +74,7 @@ hipError_t convert_f32(const Tin*, float*, int64_t, int64_t, int, int64_t, int64
 
 #define STUBS(T)                                                                                  \
   template hipError_t gemm_bias<T>(const T*, int64_t, const T*, int64_t, int, int, int, T*,      \
-                                   int64_t, const float*, const T*, int64_t, bool, hipStream_t,   \
-                                   const T*, int64_t);                                            \
+                                   int64_t, const float*, const T*, int64_t, bool, hipStream_t);  \
   template hipError_t gemm_bias_split<T>(const T*, int64_t, int, const T*, int64_t, const T*,   \
                                          int64_t, int, int, int, T*, int64_t, const float*,      \
                                          const T*, int64_t, hipStream_t);                        \
