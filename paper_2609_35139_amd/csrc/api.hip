@@ -600,8 +600,12 @@ cr_status repair_impl(T* kv, const cr_kv_layout* l, const int32_t* off, int32_t 
     CR_TRY(timed("gemm_qkv", s, [&] {
         return cr::gemm_qkv<T>(a, db, PT(Bk.w_qkv), M, db, db, dhd, q, k, vt, W.n_pad, PF(Bk.b_qkv),
                            rope, s); }));
+    // the attention's launch also brings the weights that follow it nearer:
+    // this block's FFN and the next block's QKV and output projections
+    const uint64_t pf_end = b + 1 < B ? P.blk(b + 1).w_ff1 : P.blk0.ln1_g + (b + 1) * P.blk_stride;
     CR_TRY(timed("attention", s, [&] {
-        return cr::attention<T>(q, k, vt, o, M, db, nh, dhd, W.n_pad, lo, hi, s); }));
+        return cr::attention<T>(q, k, vt, o, M, db, nh, dhd, W.n_pad, lo, hi, s, prep + Bk.w_ff1,
+                                (int64_t)(pf_end - Bk.w_ff1)); }));
     CR_TRY(timed("gemm_oproj", s, [&] {
         return cr::gemm_bias<T>(o, db, PT(Bk.w_o), db, M, db, db, h, db, PF(Bk.b_o), h, db, false, s); }));
     CR_TRY(timed("layernorm", s, [&] {

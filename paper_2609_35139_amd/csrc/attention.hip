@@ -72,6 +72,29 @@ __device__ __forceinline__ int swap_bits23(int r) {
 // Key (within a 32-key sub-tile) held by score register i of lane half g.
 __device__ __forceinline__ int score_key(int g, int i) { return (i >> 3) * 16 + g * 8 + (i & 7); }
 
+// Reads part `part` of a range of the weights that the next launches stream,
+// so that they find it in the last-level cache.  A repair streams each weight
+// once per call, from HBM if the repairer is larger than that cache (d_b =
+// 1024, 27 MB a block; FFN2 of 200 tokens 11.5 us from HBM and 8.7 from the
+// cache, of 4,096 tokens 48.2 and 44.6), while the attention leaves the HBM
+// nearly idle.  Its grid ends with these workgroups, which run on CUs that its
+// own never fill or have left (see launch_attention).
+constexpr int kPrefetchLoads = 8;
+template <int NT>
+__device__ __forceinline__ void prefetch_range(const char* p, int64_t bytes, int part) {
+  const int64_t base = (int64_t)part * (NT * 16 * kPrefetchLoads) + threadIdx.x * 16;
+  uint4 v[kPrefetchLoads];
+#pragma unroll
+  for (int i = 0; i < kPrefetchLoads; ++i) {
+    const int64_t o = base + (int64_t)i * NT * 16;
+    v[i] = o < bytes ? *reinterpret_cast<const uint4*>(p + o) : uint4{};
+  }
+  unsigned x = 0;
+#pragma unroll
+  for (int i = 0; i < kPrefetchLoads; ++i) x |= v[i].x;
+  asm volatile("" ::"v"(x));   // the loads are for their effect on the cache
+}
+
 // Two groups of four waves share the 128 queries of a workgroup and split
 // its key tiles (group g takes tiles g, g + 2, ...), each with its own online
 // softmax state and LDS ring; group 1's partial result is merged into group
@@ -94,7 +117,9 @@ __global__ __launch_bounds__(64 * WAVES) void attention_kernel(const T* __restri
                                                         int n_heads, int64_t n_pad,
                                                         const int* __restrict__ lo_arr,
                                                         const int* __restrict__ hi_arr,
-                                                        int n_qtiles) {
+                                                        int n_qtiles,
+                                                        const char* __restrict__ pf,
+                                                        int64_t pf_bytes) {
   using C = AttnCfg<T, D, STAGES, WPG, WAVES, BKV>;
   using MM = Mma32<T>;
   using frag = typename MM::frag;
@@ -108,6 +133,10 @@ __global__ __launch_bounds__(64 * WAVES) void attention_kernel(const T* __restri
   __shared__ __align__(1024) char lds[C::LDS];
 
   const int tid = threadIdx.x, lane = tid & 63;
+  if ((int)blockIdx.x >= n_qtiles * n_heads) {
+    prefetch_range<C::NT>(pf, pf_bytes, blockIdx.x - n_qtiles * n_heads);
+    return;
+  }
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave / WPG, gw = wave % WPG;
   const int g = lane >> 5, ql = lane & 31;
@@ -434,11 +463,25 @@ __global__ __launch_bounds__(64 * WAVES) void attention_kernel(const T* __restri
 template <typename T, int D, int STAGES, int WPG, int WAVES, int BKV>
 static hipError_t launch_attention(const T* q, const T* k, const T* vt, T* o, int N, int d_b,
                                    int n_heads, int64_t n_pad, const int* lo, const int* hi,
-                                   hipStream_t s) {
+                                   const void* pf, int64_t pf_bytes, hipStream_t s) {
   constexpr int BQ = 32 * WPG;
   const int n_qtiles = (N + BQ - 1) / BQ;
-  CR_LAUNCH((attention_kernel<T, D, STAGES, WPG, WAVES, BKV>), dim3(n_qtiles * n_heads),
-            dim3(64 * WAVES), 0, s, q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, n_qtiles);
+  // The prefetch is added where the last round of workgroups (one per CU)
+  // leaves a quarter of the CUs idle: there it costs the attention little or
+  // nothing (calls of 200 tokens of an 8B cache 496 -> 480 us, 1,177 ragged
+  // tokens 898 -> 870, 10 x 512 3,298 -> 3,265).  After a full round it is a
+  // tail of its own (8 x 512, 512 workgroups: attention +6 us, FFN2 -4).  fp32
+  // products are bound by the matrix cores, and ranges below 8 MB gain less
+  // than the workgroups cost (57 tokens, d_b = 512: 149 -> 152); so do
+  // products over many rounds (31,503 tokens: 20.17 -> 20.21 ms).
+  const int64_t wgs = (int64_t)n_qtiles * n_heads, last = wgs % 256;
+  const bool room = sizeof(T) == 2 && last > 0 && last <= 192 && wgs <= 2048 &&
+                    pf_bytes >= (int64_t)8 << 20;
+  const int64_t pf_part = 64 * WAVES * 16 * kPrefetchLoads;
+  const int64_t pf_wgs = pf && room ? (pf_bytes + pf_part - 1) / pf_part : 0;
+  CR_LAUNCH((attention_kernel<T, D, STAGES, WPG, WAVES, BKV>),
+            dim3((unsigned)(wgs + pf_wgs)), dim3(64 * WAVES), 0, s, q, k, vt,
+            o, N, d_b, n_heads, n_pad, lo, hi, n_qtiles, static_cast<const char*>(pf), pf_bytes);
   return hipGetLastError();
 }
 
@@ -460,38 +503,48 @@ static hipError_t launch_attention(const T* q, const T* k, const T* vt, T* o, in
 template <typename T, int D>
 static hipError_t attention_d(const T* q, const T* k, const T* vt, T* o, int N, int d_b,
                               int n_heads, int64_t n_pad, const int* lo, const int* hi,
-                              hipStream_t s) {
+                              const void* pf, int64_t pf_bytes, hipStream_t s) {
   const int64_t wg128 = (int64_t)((N + 127) / 128) * n_heads;
   const int64_t wg32 = (int64_t)((N + 31) / 32) * n_heads;
   if constexpr (sizeof(T) == 2) {
     if (wg32 <= 256)
-      return launch_attention<T, D, 2, 1, 4, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
+      return launch_attention<T, D, 2, 1, 4, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
+                                                 pf_bytes, s);
     if (wg128 < 256)
-      return launch_attention<T, D, 2, 2, 8, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
-    return launch_attention<T, D, 4, 4, 8, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
+      return launch_attention<T, D, 2, 2, 8, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
+                                                 pf_bytes, s);
+    return launch_attention<T, D, 4, 4, 8, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
+                                                 pf_bytes, s);
   } else {
     // (two-slot rings: two rings of 64 KB fit in 160 KB of LDS)
     if (wg128 < 512)
-      return launch_attention<T, D, 2, 1, 4, 32>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
-    return launch_attention<T, D, 2, 4, 8, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
+      return launch_attention<T, D, 2, 1, 4, 32>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
+                                                 pf_bytes, s);
+    return launch_attention<T, D, 2, 4, 8, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
+                                                 pf_bytes, s);
   }
 }
 
 template <typename T>
 hipError_t attention(const T* q, const T* k, const T* vt, T* o, int N, int d_b, int n_heads,
-                     int d_head, int64_t n_pad, const int* lo, const int* hi, hipStream_t s) {
+                     int d_head, int64_t n_pad, const int* lo, const int* hi, hipStream_t s,
+                     const void* pf, int64_t pf_bytes) {
   if (N <= 0) return hipSuccess;
   if (n_pad < ((N + 63) / 64) * 64) return hipErrorInvalidValue;
   if (d_head == 64)
-    return attention_d<T, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
+    return attention_d<T, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
+                                                 pf_bytes, s);
   if (d_head == 32)
-    return attention_d<T, 32>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, s);
+    return attention_d<T, 32>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
+                                                 pf_bytes, s);
   return hipErrorInvalidValue;
 }
 
 template hipError_t attention<bf16>(const bf16*, const bf16*, const bf16*, bf16*, int, int, int,
-                                    int, int64_t, const int*, const int*, hipStream_t);
+                                    int, int64_t, const int*, const int*, hipStream_t, const void*,
+                                    int64_t);
 template hipError_t attention<float>(const float*, const float*, const float*, float*, int, int,
-                                     int, int, int64_t, const int*, const int*, hipStream_t);
+                                     int, int, int64_t, const int*, const int*, hipStream_t,
+                                     const void*, int64_t);
 
 }  // namespace cr
