@@ -205,15 +205,23 @@ hipError_t compress_segments(const T* kv, KvStrides ks, int n_layers, const T* w
                              hipStream_t s) {
   if (N <= 0) return hipSuccess;
   const int S = 2 * n_layers * ks.n_kv_heads;
-  // four 16-token blocks per wave (bf16) once the grid still fills the chip
-  // several times over; one block otherwise and for fp32 (register budget)
-  const bool wide = sizeof(T) == 2 && (int64_t)((N + 63) / 64) * ((S + 3) / 4) >= 1024;
+  // 16-token blocks per wave: four once the grid still has two workgroups per
+  // CU, two once it has one, as long as the registers last (fp32: two, heads
+  // of at most 128); else one.  More blocks keep more cache reads in flight per
+  // wave and use each weight fragment more often, but leave CUs idle in a small
+  // grid (144 segments of 128; us on 1, 2 and 4 blocks: 57 tokens 4.0, 4.5,
+  // 5.8; 512 tokens 10.5, 9.4, 10.1; 1,177 tokens 19.9, 16.9, 15.2; 512
+  // segments, 200 tokens 14.4, 13.2, 11.2; fp32, 512 tokens 22.3 and 21.0).
+  auto grid = [&](int tb) { return (int64_t)((N + 16 * tb - 1) / (16 * tb)) * ((S + 3) / 4); };
+  const bool four = sizeof(T) == 2 && grid(4) >= 512;
+  const bool two = (sizeof(T) == 2 || ks.head_dim <= 128) && grid(2) >= 250;
 #define CR_COMPRESS_TB(DH, TB)                                                                 \
   CR_LAUNCH((compress_segments_kernel<T, DH, TB>), dim3((N + 16 * TB - 1) / (16 * TB), (S + 3) / 4), \
             dim3(256), 0, s, kv, ks, wseg, bseg, U, ldu, d_seg, N, S, S * d_seg)
 #define CR_COMPRESS(DH)                                                                        \
   case DH:                                                                                     \
-    if (wide) CR_COMPRESS_TB(DH, (sizeof(T) == 2 ? 4 : 1));                                    \
+    if (four) CR_COMPRESS_TB(DH, (sizeof(T) == 2 ? 4 : 1));                                    \
+    else if (two) CR_COMPRESS_TB(DH, (sizeof(T) == 2 || DH <= 128 ? 2 : 1));                   \
     else CR_COMPRESS_TB(DH, 1);                                                                \
     break;
   switch (ks.head_dim) {

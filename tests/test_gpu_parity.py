@@ -149,6 +149,22 @@ def test_parity_on_large_tiles(n, cfg):
     assert_parity(gpu_repair(inp), oracle_repair(inp), W.kv_layer_major_to_canonical(inp.kv), w)
 
 
+@pytest.mark.parametrize("n,dh,dtype", [
+    (500, 96, "bf16"),     # 17 segment groups: two token blocks per wave
+    (500, 128, "f32"),
+    (500, 160, "f32"),     # (one: the registers do not last for two)
+    (1950, 96, "bf16"),    # four
+    (200, 128, "bf16"),    # one
+])
+def test_compression_token_blocks(n, dh, dtype):
+    """Token blocks per wave of the segment projections, with a last segment
+    group of two and a ragged last block."""
+    w = small_workload(((n // 3, n - n // 3 - 7), (7,)), seed=23, dtype=dtype, L=11, H=3, dh=dh,
+                       E=64, d_c=64, d_b=128, n_heads=2, d_seg=20, n_blocks=1, ffn_mult=1)
+    inp = W.make_inputs(w)
+    assert_parity(gpu_repair(inp), oracle_repair(inp), W.kv_layer_major_to_canonical(inp.kv), w)
+
+
 def test_empty_batch_is_a_no_op():
     """Requests whose chunks are all empty: nothing is launched, the call
     succeeds and the cache buffer is untouched."""
