@@ -1274,6 +1274,13 @@ struct IsPhase { static constexpr bool value = false; };
 template <typename T, int TM, int TN, int WM, int WN>
 struct IsPhase<PhaseTile<T, TM, TN, WM, WN>> { static constexpr bool value = true; };
 
+// The phase kernel addresses a tile's rows by 32-bit byte offsets from its
+// first row (rows up to 8 MB apart: every layout but compressions of hundreds
+// of thousands of segments).
+static inline bool phase_offsets(int64_t ld, size_t esize) {
+  return 256 * ld * (int64_t)esize < ((int64_t)1 << 31);
+}
+
 static inline int64_t grid_tiles(int64_t M, int64_t N, int bm, int bn) {
   return ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
 }
@@ -1289,6 +1296,9 @@ static hipError_t launch_tiled(const T* A, int64_t lda, const T* B, int64_t ldb,
     return hipErrorInvalidValue;
   if (SPLIT && (!sp.a2 || sp.k1 <= 0 || sp.k1 >= K || sp.k1 % G::BK != 0 ||
                 sp.lda2 % G::VEC != 0 || reinterpret_cast<uintptr_t>(sp.a2) % 16 != 0))
+    return hipErrorInvalidValue;
+  if (IsPhase<G>::value && !(phase_offsets(lda, sizeof(T)) && phase_offsets(ldb, sizeof(T)) &&
+                             phase_offsets(sp.lda2, sizeof(T))))
     return hipErrorInvalidValue;
   const int64_t tiles = grid_tiles(epi.rows(M), N, G::BM, G::BN);
   if (tiles >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
@@ -1367,7 +1377,9 @@ static hipError_t launch(const T* A, int64_t lda, const T* B, int64_t ldb, int M
       if (tiles > 256 && fits(256, 128) && K >= 2048) CR_TILED(GemmTile<T, 4, 2, 3, 2, 2, 2>);
     }
     if constexpr (Epi::kWide) {
-      if (kWideGain * round_fill(grid_tiles(rows, N, 256, 256), 256) >= fill128)
+      if (kWideGain * round_fill(grid_tiles(rows, N, 256, 256), 256) >= fill128 &&
+          phase_offsets(lda, sizeof(T)) && phase_offsets(ldb, sizeof(T)) &&
+          phase_offsets(sp.lda2, sizeof(T)))
         CR_TILED(PhaseTile<T, 4, 2, 2, 4>);
     }
     if (tiles <= 256 && K >= 2048) CR_TILED(GemmTile<T, 2, 2, 4, 2, 2, 2>);
