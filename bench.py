@@ -22,15 +22,16 @@ METRIC = "repair latency ms + repaired doc tokens/s, 8×512-token chunks, Qwen2.
 PEAK = {"bf16_tflops": 2500.0, "f32_tflops": 157.3, "hbm_gbs": 8000.0}
 
 # kernel class (as reported by cr_profile_read) -> kernel function it launches
+# (gemm_*_kernel: the nt, phase or skinny GEMM, chosen by shape)
 FUNCTION_OF = {
-    "gemm_compress": "gemm_nt_kernel<EpiBias>",
-    "gemm_fuse": "gemm_nt_kernel<EpiBias>",
-    "gemm_oproj": "gemm_nt_kernel<EpiBias>", "gemm_ffn1": "gemm_nt_kernel<EpiBias>",
+    "gemm_compress": "gemm_*_kernel<EpiBias>",
+    "gemm_fuse": "gemm_*_kernel<EpiBias>",
+    "gemm_oproj": "gemm_*_kernel<EpiBias>", "gemm_ffn1": "gemm_*_kernel<EpiBias>",
     # the QKV projection runs on 256x192 tiles of whole heads (EpiQKVh) or on
-    # 128x128 tiles in the weights' column order (EpiQKV), whichever fills
-    # the grid's rounds better for the workload
-    "gemm_ffn2": "gemm_nt_kernel<EpiBias>", "gemm_qkv": "gemm_nt_kernel<EpiQKVh|EpiQKV>",
-    "gemm_expand": "gemm_nt_kernel<EpiExpand>", "attention": "attention_kernel",
+    # tiles in the weights' column order (EpiQKV), whichever fills the grid's
+    # rounds better for the workload
+    "gemm_ffn2": "gemm_*_kernel<EpiBias>", "gemm_qkv": "gemm_*_kernel<EpiQKVh|EpiQKV>",
+    "gemm_expand": "gemm_*_kernel<EpiExpand>", "attention": "attention_kernel",
     "layernorm": "layernorm_kernel", "compress_segments": "compress_segments_kernel",
     "schedule": "schedule_kernel",
 }

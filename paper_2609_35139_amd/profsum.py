@@ -71,7 +71,8 @@ def short_name(n):
     n = re.sub(r"\(.*", "", n)
     for k in ("EpiBias", "EpiQKVh", "EpiQKV", "EpiExpandRope", "EpiExpand"):
         if k in n:
-            return "gemm_nt_kernel<" + k + ">"
+            kernel = re.search(r"gemm_[a-z]+_kernel", n)
+            return (kernel.group(0) if kernel else "gemm") + "<" + k + ">"
     m = re.search(r"cr::(\w+)|_ZN2cr\d+(\w+?)I|_ZN2cr\d+(\w+)E", n)
     return (m.group(1) or m.group(2) or m.group(3)) if m else n[:40]
 
