@@ -272,3 +272,17 @@ def test_attention_tilings(n, heads, d_b, dtype, name):
                            dtype=dtype, L=1, H=1, dh=64, E=64, d_c=64, d_b=d_b, n_heads=heads,
                            d_seg=8, n_blocks=1))
     assert_parity(gpu_repair(inp, options=Options(mask=name)), oracle_repair(inp, mask=name), X, w)
+
+
+@pytest.mark.parametrize("n,H", [
+    (4300, 4),      # 1,024 output columns: the rotating output add on 192x128 tiles
+    (250, 1),       # 256: one round of 128-column tiles
+])
+def test_global_placement_on_wide_heads(n, H):
+    from paper_2609_35139_amd.binding import Options
+    w, inp, X = _case(dict(lengths=((n // 2, n - n // 2 - 9), (9,)), dtype="bf16", L=1, H=H,
+                           dh=128, E=64, d_c=64, d_b=128, n_heads=2, d_seg=8, n_blocks=1))
+    Y = gpu_repair(inp, options=Options(global_rope=dict(theta=1e4), position_offset=[5, 900]))
+    Yr = oracle_repair(inp, global_rope=dict(inv_freq=_freqs(128, 1e4), scale=1.0,
+                                             position_offset=[5, 900]))
+    assert_parity(Y, Yr, X, w)
