@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "launch.h"
+#include "rules.h"
 
 namespace cr {
 
@@ -1281,10 +1282,6 @@ static inline bool phase_offsets(int64_t ld, size_t esize) {
   return 256 * ld * (int64_t)esize < ((int64_t)1 << 31);
 }
 
-static inline int64_t grid_tiles(int64_t M, int64_t N, int bm, int bn) {
-  return ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-}
-
 template <typename T, typename G, typename Epi, bool SPLIT = false>
 static hipError_t launch_tiled(const T* A, int64_t lda, const T* B, int64_t ldb, int M, int N,
                                int K, const Epi& epi, hipStream_t s, ASplit<T> sp = {}) {
@@ -1462,9 +1459,7 @@ hipError_t gemm_expand(const T* A, int64_t lda, const T* B, int M, int N, int K,
   }
   EpiExpand<T> e{kv, ks, bias, sigma, mode, keep, kv_out, ks_out};
   if constexpr (sizeof(T) == 2) {
-    const int64_t wide = grid_tiles(M, N, 256, 256), tiles128 = grid_tiles(M, N, 128, 128);
-    const double fill128 = round_fill(tiles128, tiles128 <= 256 ? 256 : 512);
-    if (kWideGain * round_fill(wide, 256) >= fill128)
+    if (expand_on_256(M, N, K))
       return launch_tiled<T, PhaseTile<T, 4, 2, 2, 4>>(A, lda, B, K, M, N, K, e, s);
   }
   return launch<T>(A, lda, B, K, M, N, K, e, s);

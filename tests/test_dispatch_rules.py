@@ -1,0 +1,54 @@
+"""The size rules that choose between kernels, against the times of both sides.
+
+rules.h is plain host code: it is compiled here by the host compiler.  Every
+row of a table holds the measured microseconds of each choice at one shape;
+the rule may not take one that is more than a few per cent slower than the
+best (the spread between boxes is about 2%)."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2609_35139_amd", "csrc")
+SHIM = """
+#include "rules.h"
+extern "C" {
+int expand_on_256(long M, long N, int K) { return cr::expand_on_256(M, N, K); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, lib = d / "rules.cpp", d / "rules.so"
+    src.write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
+                    str(src), "-o", str(lib)], check=True)
+    return ctypes.CDLL(str(lib))
+
+
+# rows, columns, K: us on 128-column tiles, on 256-column tiles
+EXPAND = [
+    (200, 18432, 512, 13.8, 20.9), (1100, 18432, 512, 41.7, 44.1), (1500, 18432, 512, 50.5, 47.2),
+    (1920, 18432, 512, 63.4, 70.1), (2690, 18432, 512, 86.0, 94.3), (3200, 18432, 512, 101.3, 97.0),
+    (3600, 18432, 512, 110.3, 116.5), (8192, 18432, 512, 263.0, 253.0),
+    (512, 18432, 1024, 43.2, 34.1), (800, 18432, 1024, 46.4, 66.9), (1280, 18432, 1024, 69.1, 73.8),
+    (2300, 18432, 1024, 121.3, 111.6), (4096, 18432, 1024, 201.3, 189.3),
+    (5120, 18432, 1024, 242.8, 224.9), (8192, 18432, 1024, 398.7, 349.8),
+    (57, 65536, 1024, 28.0, 36.2), (128, 65536, 1024, 33.0, 40.1), (135, 65536, 1024, 47.8, 40.5),
+    (320, 65536, 1024, 70.5, 75.1), (640, 65536, 1024, 117.4, 112.7),
+    (5120, 65536, 1024, 880.5, 762.3),
+    (1920, 18432, 256, 46.3, 54.4), (3200, 18432, 256, 74.3, 75.9), (8192, 18432, 128, 140.8, 176.3),
+    (200, 15360, 512, 9.8, 20.1), (2000, 15360, 1024, 89.9, 78.8),
+    (1500, 18432, 1536, 113.4, 96.0), (2690, 18432, 2048, 247.6, 229.7),
+    (800, 18432, 2048, 77.0, 107.5),
+]
+
+
+@pytest.mark.parametrize("M,N,K,small,wide", EXPAND)
+def test_output_add_takes_the_faster_tiles(rules, M, N, K, small, wide):
+    taken = wide if rules.expand_on_256(ctypes.c_long(M), ctypes.c_long(N), K) else small
+    assert taken <= 1.05 * min(small, wide)

@@ -136,10 +136,14 @@ def test_parity_at_tile_boundaries(n, dtype):
     (4800, dict()),
     # FFN2 and the fusion on 256x128 tiles of two K groups
     (6200, dict(E=2048)),
-    # the output add on 256x256 tiles with the shortest K (two slabs), rows ragged
+    # the output add at shallow K (two and four slabs), on 128x128 tiles
     (1000, dict(L=8, H=8, dh=128, d_b=128, n_heads=2)),
-    # ... and four slabs, into columns that are no multiple of the tile
     (1000, dict(L=11, H=5, dh=96, d_c=64, d_b=256, n_heads=4)),
+    # ... on 256x256 tiles, rows ragged, and into columns that are no multiple of the tile
+    (1000, dict(L=8, H=8, dh=128, d_b=512, n_heads=8)),
+    (1000, dict(L=11, H=5, dh=96, d_c=64, d_b=512, n_heads=8)),
+    # ... and one tile row of a wide cache: 128x128 tiles, two workgroups per CU
+    (100, dict(L=20, H=8, dh=128, d_b=512, n_heads=8)),
 ])
 def test_parity_on_large_tiles(n, cfg):
     base = dict(dtype="bf16", L=1, H=2, dh=64, E=64, d_c=64, d_b=1024, n_heads=16, d_seg=8,
@@ -161,6 +165,16 @@ def test_compression_token_blocks(n, dh, dtype):
     group of two and a ragged last block."""
     w = small_workload(((n // 3, n - n // 3 - 7), (7,)), seed=23, dtype=dtype, L=11, H=3, dh=dh,
                        E=64, d_c=64, d_b=128, n_heads=2, d_seg=20, n_blocks=1, ffn_mult=1)
+    inp = W.make_inputs(w)
+    assert_parity(gpu_repair(inp), oracle_repair(inp), W.kv_layer_major_to_canonical(inp.kv), w)
+
+
+def test_two_slab_product_on_256_row_tiles():
+    """FFN1 of d_b = 128 and 2,048 columns: K is two slabs of the two-phase
+    kernel (its peeled loop ends alone), 256 tiles, the last row of them ragged."""
+    w = small_workload(((500, 1, 300), (511,)) * 6 + ((127,),), seed=31, dtype="bf16", L=1, H=1,
+                       dh=64, E=64, d_c=64, d_b=128, n_heads=2, d_seg=8, n_blocks=1, ffn_mult=16)
+    assert 7936 < w.n_tokens < 8192
     inp = W.make_inputs(w)
     assert_parity(gpu_repair(inp), oracle_repair(inp), W.kv_layer_major_to_canonical(inp.kv), w)
 
