@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "launch.h"
+#include "rules.h"
 
 namespace cr {
 LaunchEvents& launch_events() {
@@ -601,11 +602,14 @@ cr_status repair_impl(T* kv, const cr_kv_layout* l, const int32_t* off, int32_t 
         return cr::gemm_qkv<T>(a, db, PT(Bk.w_qkv), M, db, db, dhd, q, k, vt, W.n_pad, PF(Bk.b_qkv),
                            rope, s); }));
     // the attention's launch also brings the weights that follow it nearer:
-    // this block's FFN and the next block's QKV and output projections
+    // this block's FFN and the next block's QKV and output projections (fp32
+    // products are bound by the matrix cores)
     const uint64_t pf_end = b + 1 < B ? P.blk(b + 1).w_ff1 : P.blk0.ln1_g + (b + 1) * P.blk_stride;
+    const int64_t pf_bytes = (int64_t)(pf_end - Bk.w_ff1);
+    const bool pf = sizeof(T) == 2 && cr::prefetch_pays(pf_bytes, (int64_t)P.total);
     CR_TRY(timed("attention", s, [&] {
-        return cr::attention<T>(q, k, vt, o, M, db, nh, dhd, W.n_pad, lo, hi, s, prep + Bk.w_ff1,
-                                (int64_t)(pf_end - Bk.w_ff1)); }));
+        return cr::attention<T>(q, k, vt, o, M, db, nh, dhd, W.n_pad, lo, hi, s,
+                                pf ? prep + Bk.w_ff1 : nullptr, pf_bytes); }));
     CR_TRY(timed("gemm_oproj", s, [&] {
         return cr::gemm_bias<T>(o, db, PT(Bk.w_o), db, M, db, db, h, db, PF(Bk.b_o), h, db, false, s); }));
     CR_TRY(timed("layernorm", s, [&] {

@@ -32,6 +32,7 @@
 #include <type_traits>
 
 #include "launch.h"
+#include "rules.h"
 
 namespace cr {
 
@@ -466,19 +467,9 @@ static hipError_t launch_attention(const T* q, const T* k, const T* vt, T* o, in
                                    const void* pf, int64_t pf_bytes, hipStream_t s) {
   constexpr int BQ = 32 * WPG;
   const int n_qtiles = (N + BQ - 1) / BQ;
-  // The prefetch is added where the last round of workgroups (one per CU)
-  // leaves a quarter of the CUs idle: there it costs the attention little or
-  // nothing (calls of 200 tokens of an 8B cache 496 -> 480 us, 1,177 ragged
-  // tokens 898 -> 870, 10 x 512 3,298 -> 3,265).  After a full round it is a
-  // tail of its own (8 x 512, 512 workgroups: attention +6 us, FFN2 -4).  fp32
-  // products are bound by the matrix cores, and ranges below 8 MB gain less
-  // than the workgroups cost (57 tokens, d_b = 512: 149 -> 152); so do
-  // products over many rounds (31,503 tokens: 20.17 -> 20.21 ms).
-  const int64_t wgs = (int64_t)n_qtiles * n_heads, last = wgs % 256;
-  const bool room = sizeof(T) == 2 && last > 0 && last <= 192 && wgs <= 2048 &&
-                    pf_bytes >= (int64_t)8 << 20;
+  const int64_t wgs = (int64_t)n_qtiles * n_heads;
   const int64_t pf_part = 64 * WAVES * 16 * kPrefetchLoads;
-  const int64_t pf_wgs = pf && room ? (pf_bytes + pf_part - 1) / pf_part : 0;
+  const int64_t pf_wgs = pf && prefetch_fits(wgs) ? ceil_div(pf_bytes, pf_part) : 0;
   CR_LAUNCH((attention_kernel<T, D, STAGES, WPG, WAVES, BKV>),
             dim3((unsigned)(wgs + pf_wgs)), dim3(64 * WAVES), 0, s, q, k, vt,
             o, N, d_b, n_heads, n_pad, lo, hi, n_qtiles, static_cast<const char*>(pf), pf_bytes);

@@ -34,4 +34,34 @@ inline bool expand_on_256(int64_t M, int64_t N, int K) {
   return 2.0 * (double)wide <= expand_gain(K) * (double)small;
 }
 
+// Weights that the attention's launch brings into the last-level cache ahead
+// of the products that stream them: `range` bytes of a repairer of `total`.
+// Only where a repairer is larger than that cache (256 MB), since otherwise its
+// weights stay there from call to call (162 MB, 57 tokens: 176 us without and
+// 181 with; 82 MB: 131 and 134), and only ranges whose reading takes no longer
+// than the attention leaves the chip idle: 26 MB a block pay (267 MB, 57
+// tokens: 385 -> 347; 256: 445 -> 420; 1,500: 962 -> 898); 100 MB are read in
+// 17 us beside an attention of 5 (57 tokens: 322 and 328, 1,200: 993 and
+// 1,013), 164 MB in 28 (57: 333 and 356) and 292 MB, which the cache no longer
+// holds, twice (57: 474 and 580, 1,500: 1,893 and 2,015).  Part of such a range
+// gains nothing (32 of 100 MB: 57 tokens 324, 1,200 997), and ranges below 8 MB
+// less than the workgroups cost (57 tokens, d_b = 512: 149 and 152).
+inline bool prefetch_pays(int64_t range, int64_t total) {
+  return range >= (int64_t)8 << 20 && range <= (int64_t)32 << 20 && total > (int64_t)256 << 20;
+}
+
+// ... and where the last round of the attention's workgroups (one per CU)
+// leaves a quarter of the CUs idle: there it costs the attention little or
+// nothing (8 blocks of 26 MB, 200 tokens of an 8B cache 496 -> 480 us, 384 631
+// -> 587, 1,177 ragged tokens 898 -> 870, 10 x 512 3,298 -> 3,265; at worst
+// 288 tokens, 144 workgroups: 482 and 488).  After a full round it is a tail of
+// its own (8 x 512, 512 workgroups: attention +6 us, FFN2 -4), and over more
+// than five rounds the products no longer gain (8,900 tokens, 1,120
+// workgroups: 6,409 -> 6,371; 10,500, 1,328: 7,494 and 7,531; 15,000, 1,888:
+// 8,302 and 8,350).
+inline bool prefetch_fits(int64_t workgroups) {
+  const int64_t last = workgroups % 256;
+  return last > 0 && last <= 192 && workgroups <= 1280;
+}
+
 }  // namespace cr

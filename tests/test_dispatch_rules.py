@@ -16,6 +16,9 @@ SHIM = """
 #include "rules.h"
 extern "C" {
 int expand_on_256(long M, long N, int K) { return cr::expand_on_256(M, N, K); }
+int prefetch(long wgs, long range, long total) {
+  return cr::prefetch_pays(range, total) && cr::prefetch_fits(wgs);
+}
 }
 """
 
@@ -52,3 +55,26 @@ EXPAND = [
 def test_output_add_takes_the_faster_tiles(rules, M, N, K, small, wide):
     taken = wide if rules.expand_on_256(ctypes.c_long(M), ctypes.c_long(N), K) else small
     assert taken <= 1.05 * min(small, wide)
+
+
+MB = 1 << 20
+# attention workgroups, bytes to prefetch, bytes of the repairer: us of the call without, with
+PREFETCH = [
+    (64, 26 * MB, 267 * MB, 384.6, 347.2), (144, 26 * MB, 267 * MB, 481.6, 488.1),
+    (128, 26 * MB, 267 * MB, 444.8, 419.8), (192, 26 * MB, 267 * MB, 510.5, 494.3),
+    (384, 26 * MB, 267 * MB, 962.0, 898.3), (576, 26 * MB, 267 * MB, 2215.9, 2175.7),
+    # a repairer that stays in the cache
+    (64, 26 * MB, 162 * MB, 176.1, 181.2), (96, 14 * MB, 82 * MB, 131.0, 134.3),
+    # ranges that take longer to read than the attention
+    (64, 100 * MB, 512 * MB, 321.7, 328.2), (64, 164 * MB, 604 * MB, 333.4, 355.6),
+    (64, 292 * MB, 989 * MB, 473.5, 579.7), (640, 292 * MB, 989 * MB, 1671.5, 1800.2),
+    (64, 6 * MB, 53 * MB, 149.0, 152.0),
+    # many rounds
+    (1888, 26 * MB, 267 * MB, 8301.8, 8369.6),
+]
+
+
+@pytest.mark.parametrize("wgs,range_,total,without,with_", PREFETCH)
+def test_weights_are_prefetched_where_that_is_faster(rules, wgs, range_, total, without, with_):
+    on = rules.prefetch(ctypes.c_long(wgs), ctypes.c_long(range_), ctypes.c_long(total))
+    assert (with_ if on else without) <= 1.015 * min(without, with_)
