@@ -14,24 +14,29 @@ inline int64_t grid_tiles(int64_t M, int64_t N, int bm, int bn) {
 // launch(), 128x128 ones of which two share a CU.  Compared by the time of
 // their rounds over the chip, so that rows of padding count: a round of 256
 // wide tiles covers what two rounds of 512 small ones do, and takes less time
-// the deeper the product, since its epilogue, in which nothing overlaps, costs
-// as much as the loop over some 700 k, the small tiles' as much as 265.  Over
-// 16 to 8,192 rows, 15,360 to 65,536 columns and K from 128 to 2,048 the tiles
-// not taken are at most 5% faster; us on 128- and 256-column ones:
+// the deeper the product (its epilogue, in which nothing overlaps, costs as
+// much as the loop over some 700 k, the small tiles' as much as 265).  The last
+// round of many small ones overlaps the one before it, so it counts for less
+// when it is ragged.  Below K = 512 the small tiles are always as fast.  Over 16
+// to 8,192 rows, 15,360 to 65,536 columns and K from 128 to 2,048 the tiles not
+// taken are at most 5% faster; us on 128- and 256-column ones:
 //   equal rounds, 3,200 x 18,432: K = 256: 74 and 76, 512: 101 and 97,
 //     1,024: 160 and 148, 2,048: 271 and 236;
 //   1,920 x 18,432 (5 rounds and 3): K = 512: 63 and 70, 1,024: 108 and 107,
 //     1,536: 141 and 140;  2,690 rows (7 and 4): 512: 86 and 94, 2,048: 248 and
-//     230;  1,100 rows (3 and 2): 1,024: 65 and 68;
+//     230;  3,600 rows (9, ragged, and 5): 512: 110 and 117;  4,096 rows (9,
+//     full, and 5): 512: 133 and 129, 1,024: 201 and 189;
 //   65,536 columns, K = 1,024: 128 rows (1 and 1) 33 and 40, 320 rows (3 and 2)
 //     71 and 75, 600 rows (5 and 3) 115 and 112.
-inline double expand_gain(int K) { return 1.61 * (K + 265.0) / (K + 695.0); }
-
 inline bool expand_on_256(int64_t M, int64_t N, int K) {
+  if (K < 512) return false;
+  // (a grid of at most 256 small tiles runs one to a CU, on twice the waves)
   const int64_t t128 = grid_tiles(M, N, 128, 128);
-  // a grid of at most 256 tiles runs one to a CU, on twice the waves
-  const int64_t small = ceil_div(t128, 512), wide = ceil_div(grid_tiles(M, N, 256, 256), 256);
-  return 2.0 * (double)wide <= expand_gain(K) * (double)small;
+  const double full = (double)t128 / 512.0;
+  const double ragged = full + 0.5 + 0.5 / full, whole = (double)ceil_div(t128, 512);
+  const double small = ragged < whole ? ragged : whole;
+  const double wide = (double)ceil_div(grid_tiles(M, N, 256, 256), 256);
+  return 2.0 * wide <= (1.01 + K / 4880.0) * small;
 }
 
 // Weights that the attention's launch brings into the last-level cache ahead

@@ -37,7 +37,8 @@ def rules(tmp_path_factory):
 EXPAND = [
     (200, 18432, 512, 13.8, 20.9), (1100, 18432, 512, 41.7, 44.1), (1500, 18432, 512, 50.5, 47.2),
     (1920, 18432, 512, 63.4, 70.1), (2690, 18432, 512, 86.0, 94.3), (3200, 18432, 512, 101.3, 97.0),
-    (3600, 18432, 512, 110.3, 116.5), (8192, 18432, 512, 263.0, 253.0),
+    (3600, 18432, 512, 110.3, 116.5), (4000, 18432, 512, 133.7, 124.7),
+    (7300, 18432, 512, 219.9, 223.4), (8192, 18432, 512, 263.0, 253.0),
     (512, 18432, 1024, 43.2, 34.1), (800, 18432, 1024, 46.4, 66.9), (1280, 18432, 1024, 69.1, 73.8),
     (2300, 18432, 1024, 121.3, 111.6), (4096, 18432, 1024, 201.3, 189.3),
     (5120, 18432, 1024, 242.8, 224.9), (8192, 18432, 1024, 398.7, 349.8),
