@@ -10,7 +10,7 @@
 // inside every row's interval.
 //
 // A workgroup owns 128 queries of one head (32 per wave; 64 or 32 queries for
-// grids too small to fill the chip, see attention_d).  Scores are formed
+// grids too small to fill the chip, see attention_queries).  Scores are formed
 // transposed, S^T = K Q^T, with 32x32 MFMA atoms, so that each lane holds the
 // scores of one query: the online-softmax max and sum are register
 // reductions plus one in-register exchange with lane ^ 32.  The K rows of
@@ -469,73 +469,54 @@ static hipError_t launch_attention(const T* q, const T* k, const T* vt, T* o, in
   const int n_qtiles = (N + BQ - 1) / BQ;
   const int64_t wgs = (int64_t)n_qtiles * n_heads;
   const int64_t pf_part = 64 * WAVES * 16 * kPrefetchLoads;
-  const int64_t pf_wgs = pf && prefetch_fits(wgs) ? ceil_div(pf_bytes, pf_part) : 0;
+  const int64_t pf_wgs = pf && prefetch_fits(wgs, BQ) ? ceil_div(pf_bytes, pf_part) : 0;
   CR_LAUNCH((attention_kernel<T, D, STAGES, WPG, WAVES, BKV>),
             dim3((unsigned)(wgs + pf_wgs)), dim3(64 * WAVES), 0, s, q, k, vt,
             o, N, d_b, n_heads, n_pad, lo, hi, n_qtiles, static_cast<const char*>(pf), pf_bytes);
   return hipGetLastError();
 }
 
-// Query tiles.  A grid that leaves CUs idle, or has them all wait for the few
-// workgroups of the last chunks, is bound by one workgroup's walk over its key
-// tiles, so it takes shorter tiles and more key groups (16 heads of 64 unless
-// said; us):
-//   bf16, 32-query tiles with four one-wave groups while their grid fits the
-//     256 CUs (200 tokens 6.1 -> 5.5, 57 tokens x 8 heads 5.1 -> 4.9 and
-//     4 x 256 x 8 heads 9.1 -> 8.1 against the 64-query tiles);
-//   bf16, 64-query tiles with four two-wave groups while the 128-query grid is
-//     smaller than the chip (1,177 ragged tokens 21.9 -> 14.8, 2,500 tokens x
-//     8 heads 26.6 -> 20.4 against 128-query tiles; at 256 workgroups, 2,048
-//     tokens, both take 21.8);
-//   fp32, 32-query tiles with four groups and 32-key tiles (two-slot rings of
-//     16 KB per group) below two 128-query workgroups per CU (2 x 256 tokens x
-//     8 heads 37 -> 13.5, 2,048 x 8 heads 130 -> 55; at 512 workgroups, 4,096
-//     tokens, 297 against 358).
+// Query tiles: see attention_queries.
 template <typename T, int D>
 static hipError_t attention_d(const T* q, const T* k, const T* vt, T* o, int N, int d_b,
                               int n_heads, int64_t n_pad, const int* lo, const int* hi,
-                              const void* pf, int64_t pf_bytes, hipStream_t s) {
-  const int64_t wg128 = (int64_t)((N + 127) / 128) * n_heads;
-  const int64_t wg32 = (int64_t)((N + 31) / 32) * n_heads;
+                              int max_keys, const void* pf, int64_t pf_bytes, hipStream_t s) {
+#define CR_ATTN(...)                                                                             \
+  return launch_attention<T, D, __VA_ARGS__>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,    \
+                                             pf_bytes, s)
+  const int queries = attention_queries(N, n_heads, D, sizeof(T) == 4, max_keys);
   if constexpr (sizeof(T) == 2) {
-    if (wg32 <= 256)
-      return launch_attention<T, D, 2, 1, 4, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
-                                                 pf_bytes, s);
-    if (wg128 < 256)
-      return launch_attention<T, D, 2, 2, 8, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
-                                                 pf_bytes, s);
-    return launch_attention<T, D, 4, 4, 8, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
-                                                 pf_bytes, s);
+    if (queries == 32) CR_ATTN(2, 1, 4, 64);
+    if (queries == 64) CR_ATTN(2, 2, 8, 64);
+    CR_ATTN(4, 4, 8, 64);
   } else {
     // (two-slot rings: two rings of 64 KB fit in 160 KB of LDS)
-    if (wg128 < 512)
-      return launch_attention<T, D, 2, 1, 4, 32>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
-                                                 pf_bytes, s);
-    return launch_attention<T, D, 2, 4, 8, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
-                                                 pf_bytes, s);
+    if (queries == 32) CR_ATTN(2, 1, 4, 32);
+    CR_ATTN(2, 4, 8, 64);
   }
+#undef CR_ATTN
 }
 
 template <typename T>
 hipError_t attention(const T* q, const T* k, const T* vt, T* o, int N, int d_b, int n_heads,
-                     int d_head, int64_t n_pad, const int* lo, const int* hi, hipStream_t s,
-                     const void* pf, int64_t pf_bytes) {
+                     int d_head, int64_t n_pad, const int* lo, const int* hi, int max_keys,
+                     hipStream_t s, const void* pf, int64_t pf_bytes) {
   if (N <= 0) return hipSuccess;
   if (n_pad < ((N + 63) / 64) * 64) return hipErrorInvalidValue;
   if (d_head == 64)
-    return attention_d<T, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
-                                                 pf_bytes, s);
+    return attention_d<T, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, max_keys, pf, pf_bytes,
+                              s);
   if (d_head == 32)
-    return attention_d<T, 32>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,
-                                                 pf_bytes, s);
+    return attention_d<T, 32>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, max_keys, pf, pf_bytes,
+                              s);
   return hipErrorInvalidValue;
 }
 
 template hipError_t attention<bf16>(const bf16*, const bf16*, const bf16*, bf16*, int, int, int,
-                                    int, int64_t, const int*, const int*, hipStream_t, const void*,
-                                    int64_t);
+                                    int, int64_t, const int*, const int*, int, hipStream_t,
+                                    const void*, int64_t);
 template hipError_t attention<float>(const float*, const float*, const float*, float*, int, int,
-                                     int, int, int64_t, const int*, const int*, hipStream_t,
+                                     int, int, int64_t, const int*, const int*, int, hipStream_t,
                                      const void*, int64_t);
 
 }  // namespace cr

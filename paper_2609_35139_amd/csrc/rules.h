@@ -56,17 +56,49 @@ inline bool prefetch_pays(int64_t range, int64_t total) {
 }
 
 // ... and where the last round of the attention's workgroups (one per CU)
-// leaves a quarter of the CUs idle: there it costs the attention little or
-// nothing (8 blocks of 26 MB, 200 tokens of an 8B cache 496 -> 480 us, 384 631
-// -> 587, 1,177 ragged tokens 898 -> 870, 10 x 512 3,298 -> 3,265; at worst
-// 288 tokens, 144 workgroups: 482 and 488).  After a full round it is a tail of
+// leaves CUs idle, a quarter of them beside the short walks of 32-query tiles
+// and one in sixteen else: there it costs the attention little or nothing
+// (8 blocks of 26 MB, 200 tokens of an 8B cache 496 -> 480 us, 384 631 -> 587,
+// 850 tokens, 224 workgroups, 705 -> 677, 1,177 ragged ones 898 -> 870, 10 x 512
+// 3,298 -> 3,265; at worst 288 tokens, 144 workgroups of 32 queries: 482 and
+// 488; 400, 208 workgroups: 520 and 527).  After a full round it is a tail of
 // its own (8 x 512, 512 workgroups: attention +6 us, FFN2 -4), and over more
 // than five rounds the products no longer gain (8,900 tokens, 1,120
 // workgroups: 6,409 -> 6,371; 10,500, 1,328: 7,494 and 7,531; 15,000, 1,888:
 // 8,302 and 8,350).
-inline bool prefetch_fits(int64_t workgroups) {
+inline bool prefetch_fits(int64_t workgroups, int queries) {
   const int64_t last = workgroups % 256;
-  return last > 0 && last <= 192 && workgroups <= 1280;
+  return last > 0 && last <= (queries == 32 ? 192 : 240) && workgroups <= 1280;
+}
+
+// Attention: queries per workgroup (128 with two groups of waves splitting the
+// keys, 64 or 32 with four).  A grid that leaves CUs idle, or has them all wait
+// for the few workgroups of the last chunks, is bound by one workgroup's walk
+// over its key tiles, so it takes shorter tiles and more key groups (16 heads
+// of 64 unless said; us):
+//   bf16, 32 queries while their grid fits the 256 CUs (200 tokens 6.1 -> 5.5,
+//     57 tokens x 8 heads 5.1 -> 4.9 and 4 x 256 x 8 heads 9.1 -> 8.1 against
+//     64-query tiles);
+//   bf16, 64 queries while their grid fits the CUs (one workgroup each with
+//     heads of 64, two with heads of 32: 1,024 tokens 9.4 against 12.5), and
+//     until the 128-query grid does if a row has more than 512 keys (1,177
+//     ragged tokens 21.9 -> 14.8, 2,500 tokens x 8 heads 24.7 -> 17.6, 4,000 37.1
+//     -> 32.3; 2,000 tokens x 16 heads 21.1 -> 20.6).  Shorter walks do not repay the
+//     second workgroup on a CU (2,500 tokens x 8 heads in requests of 512: 12.6
+//     and 9.4, of 256: 10.5 and 7.0, of 100: 11.4 and 10.4; only unaligned
+//     requests of 300 to 400 whose grid hardly exceeds the CUs would: 13.7 and
+//     16.7 at 1,283 tokens);
+//   fp32, 32 queries and 32-key tiles (two-slot rings of 32 KB per group) below
+//     two 128-query workgroups per CU (2 x 256 tokens x 8 heads 37 -> 13.5,
+//     2,048 x 8 heads 130 -> 54; at 512 workgroups, 4,096 tokens, 360 and 302).
+//     From 384 on it depends on the chunks: 3,000 tokens in 512-token chunks of
+//     one request 212 against 193, in two requests of one chunk 193 against 221.
+inline int attention_queries(int64_t N, int n_heads, int d_head, bool fp32, int64_t max_keys) {
+  const int64_t wg128 = ceil_div(N, 128) * n_heads;
+  if (fp32) return wg128 < 512 ? 32 : 128;
+  if (ceil_div(N, 32) * n_heads <= 256) return 32;
+  if (ceil_div(N, 64) * n_heads <= (d_head == 32 ? 512 : 256)) return 64;
+  return wg128 <= 256 && max_keys > 512 ? 64 : 128;
 }
 
 }  // namespace cr

@@ -45,7 +45,7 @@ hipError_t gemm_expand(const T*, int64_t, const T*, int, int, int, T*, KvStrides
 }
 template <typename T>
 hipError_t attention(const T*, const T*, const T*, T*, int, int, int, int, int64_t, const int*,
-                     const int*, hipStream_t, const void*, int64_t) {
+                     const int*, int, hipStream_t, const void*, int64_t) {
   return hipErrorInvalidValue;
 }
 template <typename T>
@@ -87,7 +87,8 @@ hipError_t convert_f32(const Tin*, float*, int64_t, int64_t, int, int64_t, int64
                                      const float*, const float*, int, const int*, const float2*,  \
                                      T*, KvStrides, hipStream_t);                                 \
   template hipError_t attention<T>(const T*, const T*, const T*, T*, int, int, int, int, int64_t, \
-                                   const int*, const int*, hipStream_t, const void*, int64_t);    \
+                                   const int*, const int*, int, hipStream_t, const void*,         \
+                                   int64_t);                                                      \
   template hipError_t layernorm<T>(const T*, int64_t, T*, int64_t, const float*, const float*,   \
                                    int, int, float, hipStream_t);                                 \
   template hipError_t compress_segments<T>(const T*, KvStrides, int, const T*, const float*, T*, \
