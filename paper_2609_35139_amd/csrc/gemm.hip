@@ -78,9 +78,10 @@ struct EpiBias {
   static constexpr bool kInOrder = true;
   static constexpr bool kWide = true;
   // kCols: the narrowest column tile the epilogue works on (besides its
-  // min_cols); kSeg: output columns a thread owns per row; rows(M): output
-  // rows the grid has to cover
+  // min_cols); kSeg: output columns a thread owns per row; kDeep: K may exceed
+  // the backbone width (2,048); rows(M): output rows the grid has to cover
   static constexpr int kCols = 32, kSeg = 8;
+  static constexpr bool kDeep = true;
   static constexpr bool kBoth = true;   // two passes' Pre records fit beside a 256x256 tile
   __device__ __host__ int rows(int M) const { return M; }
   __host__ int min_cols() const { return 32; }
@@ -148,6 +149,7 @@ struct EpiBias {
 template <typename T>
 struct EpiQKV {
   static constexpr bool kWide = false;   // head-aligned tiles inside Q, K or V
+  static constexpr bool kDeep = false;
   static constexpr bool kBoth = true;
   static constexpr int kCols = 64, kSeg = 8;
   // the attention's last key tile reads K rows and V^T columns up to the next
@@ -410,6 +412,7 @@ struct EpiExpand {
   static constexpr bool kInOrder = true;
   static constexpr bool kWide = false;
   static constexpr bool kBoth = true;
+  static constexpr bool kDeep = false;
   static constexpr int kCols = 64, kSeg = 8;
   __device__ __host__ int rows(int M) const { return M; }
   __host__ int min_cols() const { return 64; }
@@ -1360,10 +1363,14 @@ static hipError_t launch(const T* A, int64_t lda, const T* B, int64_t ldb, int M
   if (fits(32, 64)) CR_TILED(SkinnyTile<T, 1, 2, 4, 2>);
   if (fits(64, 64)) {
     // (an epilogue of 16 columns per thread has no row left for eight waves)
-    if constexpr (Epi::kSeg == 8) {
-      if (!BF || K < 2560) CR_TILED(GemmTile<T, 1, 1, 4, 2, 2, 2>);
+    if constexpr (Epi::kSeg != 8) {
+      CR_TILED(SkinnyTile<T, 2, 2, 4, 2>);
+    } else {
+      if constexpr (BF && Epi::kDeep) {
+        if (K >= 2560) CR_TILED(SkinnyTile<T, 2, 2, 4, 2>);
+      }
+      CR_TILED(GemmTile<T, 1, 1, 4, 2, 2, 2>);
     }
-    CR_TILED(SkinnyTile<T, 2, 2, 4, 2>);
   }
   const int64_t tiles = grid_tiles(rows, N, 128, 128);
   const double fill128 = round_fill(tiles, tiles <= 256 ? 256 : 512);

@@ -22,7 +22,9 @@ def _rows():
 
 def test_every_source_reported():
     rows = _rows()
-    assert any("gemm_nt_kernel" in n for n, _ in rows)
+    for kernel in ("gemm_nt_kernel", "gemm_skinny_kernel", "gemm_phase_kernel",
+                   "compress_segments_kernel"):
+        assert any(kernel in n for n, _ in rows)
     assert any("attention_kernel" in n for n, _ in rows)
     assert any("layernorm_kernel" in n for n, _ in rows)
 
@@ -30,6 +32,15 @@ def test_every_source_reported():
 def test_no_kernel_spills_to_scratch():
     bad = [(n, r) for n, r in _rows() if r.get("scratch") not in ("0",)]
     assert not bad, bad
+
+
+def test_no_kernel_that_the_tile_choice_cannot_reach():
+    """64x64 tiles split over K by wave: for bf16 bias epilogues of long K, and
+    for the rotating output add, whose threads own two segments."""
+    names = [n for n, _ in _rows() if "SkinnyTileI" in n and "Li2ELi2ELi4ELi2EEE" in n]
+    bias = [n for n in names if "EpiBiasIDF16b" in n]
+    rope = [n for n in names if "EpiExpandRopeI" in n]
+    assert len(bias) == 2 and len(rope) == 2 and len(names) == 4, names
 
 
 def test_resource_remarks_parse():
