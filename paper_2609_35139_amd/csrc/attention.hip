@@ -61,7 +61,8 @@ struct AttnCfg {
   static constexpr int MLD = D + 1;
   static constexpr int MERGE_ONE = BQ * MLD * 4 + 2 * BQ * 2 * 4;
   static constexpr int MERGE_BYTES = (GROUPS - 1) * MERGE_ONE;
-  static_assert(GROUPS * WPG == WAVES && BKV % 32 == 0 && K_ROUNDS * WPG * 1024 == K_BYTES &&
+  // (64 % BKV: the last key tile stays inside the padding of K and V^T)
+  static_assert(GROUPS * WPG == WAVES && BKV % 32 == 0 && 64 % BKV == 0 && K_ROUNDS * WPG * 1024 == K_BYTES &&
                 V_ROUNDS * WPG * 1024 == V_BYTES, "wave groups");
   static constexpr int LDS = GROUPS * RING_BYTES > MERGE_BYTES ? GROUPS * RING_BYTES : MERGE_BYTES;
 };
@@ -107,9 +108,11 @@ __device__ __forceinline__ void prefetch_range(const char* p, int64_t bytes, int
 // walking a quarter of the key tiles.
 //
 // Q arrives pre-scaled by log2(e)/sqrt(d_head) (QKV epilogue), so scores are
-// in exp2 units.  K and V^T are padded with finite rows up to n_pad, so tile
-// loads need no clamping.  The tile loop is unrolled over the STAGES ring
-// slots: every LDS address is a per-lane base plus a compile-time offset.
+// in exp2 units.  K and V^T are padded with finite rows up to roundup(N, 64)
+// (a NaN there would survive a probability of zero) and key tiles start at
+// multiples of their 32 or 64 keys, so tile loads need no clamping.  The tile
+// loop is unrolled over the STAGES ring slots: every LDS address is a per-lane
+// base plus a compile-time offset.
 template <typename T, int D, int STAGES = 4, int WPG = 4, int WAVES = 8, int BKV = 64>
 __global__ __launch_bounds__(64 * WAVES) void attention_kernel(const T* __restrict__ Q,
                                                         const T* __restrict__ Kg,
@@ -172,7 +175,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_kernel(const T* __restri
   }
 
   // DMA sources (per lane) of the workgroup's first key tile: K rows are
-  // keys, V^T rows are d.  Both are padded to n_pad >= roundup(N, 64) keys.
+  // keys, V^T rows are d.  Both are padded to roundup(N, 64) keys.
   const char* ksrc[C::K_ROUNDS];
   const char* vsrc[C::V_ROUNDS];
 #pragma unroll
@@ -219,7 +222,8 @@ __global__ __launch_bounds__(64 * WAVES) void attention_kernel(const T* __restri
 #pragma unroll
   for (int i = 0; i < 16; ++i) negm[i] = 0.f;
 
-  // group-local tile i (workgroup tile 2i + grp) into ring slot SLOT
+  // group-local tile i (workgroup tile GROUPS * i + grp) into the ring slot
+  // at slot_bytes
   auto issue = [&](int i, int slot_bytes) {
     char* base = ring + slot_bytes;
     const int64_t tile = (int64_t)C::GROUPS * i + grp;
@@ -246,7 +250,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_kernel(const T* __restri
     // fragment reads and score products (-2% per launch, same results)
     __builtin_amdgcn_iglp_opt(0);
 
-    // S^T = K Q^T for two 32-key sub-tiles; all fragment reads first
+    // S^T = K Q^T for the tile's 32-key sub-tiles; all fragment reads first
     frag kf[RT][QF];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)

@@ -9,11 +9,12 @@
 // are XOR-swizzled in LDS so fragment reads are conflict-free.  The MFMA
 // takes the weight tile as its first operand, so each lane ends with four
 // consecutive output columns of one output row: the fp32 tile is staged
-// through LDS with 16-byte writes in one pass, after the epilogue has issued
-// its own global loads (bias, residuals, the stale cache), and every
-// epilogue then reads and writes whole 16-byte row segments (bias, GELU,
-// residual adds, RoPE, transposed V, the strided output add into the KV
-// cache with optional global placement of the keys).
+// through LDS with 16-byte writes (in one pass, or in two by gemm_phase_kernel),
+// and every epilogue then reads and writes whole 16-byte row segments (bias,
+// GELU, residual adds, RoPE, transposed V, the strided output add into the KV
+// cache with optional global placement of the keys).  Its own global loads
+// (bias, residuals, the stale cache) go out before the main loop in
+// gemm_nt_kernel and when it ends in the other two kernels.
 #include <algorithm>
 #include <type_traits>
 
@@ -144,8 +145,9 @@ struct EpiBias {
   }
 };
 
-// QKV projection in the weights' own column order [Q | K | V] on 128-column
-// tiles (each inside Q, K or V and head-aligned, d_b % 128 == 0).
+// QKV projection in the weights' own column order [Q | K | V] on tiles of 64,
+// 128 or 256 columns (each inside Q, K or V, since d_b is a multiple of them,
+// and head-aligned).
 template <typename T>
 struct EpiQKV {
   static constexpr bool kWide = false;   // head-aligned tiles inside Q, K or V
@@ -179,8 +181,9 @@ struct EpiQKV {
       // Q or K: rotate pairs (i, i + d_head/2) of every head by pos * freq_i.
       // The tile is head-aligned and never straddles Q/K (d_b % COLS == 0).
       // Q leaves scaled by log2(e)/sqrt(d_head) (the attention works in exp2
-      // units); K rows in [M, n_pad) get finite values from clamped rows
-      // (padding read by the attention's last key tile).
+      // units); the tile's K rows in [M, n_pad) get finite values from clamped
+      // rows (padding up to roundup(M, 64) is read by the attention's last key
+      // tile).
       using S = SegMap<ROWS, COLS, NT>;
       const bool is_q = n0 < d_b;
       T* dst = is_q ? q : k;
@@ -231,8 +234,8 @@ struct EpiQKV {
     } else {
       // V: written transposed, vt[head][d][token], 8 tokens per 16-byte
       // store.  Consecutive threads take consecutive columns, so the column
-      // reads of the staged tile are conflict-free.  Rows in [M, n_pad) hold
-      // values computed from clamped rows: finite padding.
+      // reads of the staged tile are conflict-free.  The tile's rows in
+      // [M, n_pad) hold values computed from clamped rows: finite padding.
       constexpr int RSEG = ROWS / 8;
       for (int idx = threadIdx.x; idx < COLS * RSEG; idx += NT) {
         const int c = idx % COLS, r = (idx / COLS) * 8;
@@ -729,12 +732,11 @@ __global__ __launch_bounds__(G::NT) void gemm_nt_kernel(const T* __restrict__ A,
     for (int o = 0; o < G::OPS; ++o) dma_op(o, kt, stage);
   };
   // Spread issue (the 8-wave tiles, whose 3- and 4-slab rings give a refill
-  // two or three iterations to land): the refill goes out in equal shares over the
-  // slab's k-steps, each share after that step's fragment reads for the next
+  // two or three iterations to land): the refill goes out in equal shares over
+  // the slab's k-steps, each share after that step's fragment reads for the next
   // step (a DMA writes LDS, so the compiler keeps it behind every earlier
   // read) and among its products, instead of as a burst after the barrier.
-  // Every
-  // slab is loaded, past the end as a copy of the last slab into a stage
+  // Every slab is loaded, past the end as a copy of the last slab into a stage
   // nobody reads again, so each iteration issues the same OPS operations and
   // waits for the same count.  (2-slab rings keep the burst: their refill
   // must land within the iteration.)
@@ -952,7 +954,8 @@ __global__ __launch_bounds__(G::NT) void gemm_skinny_kernel(const T* __restrict_
 #pragma unroll
   for (int r = 0; r < G::B_OPS; ++r) {
     const int row = r * 8 + (lane >> 3), ch = ((lane & 7) ^ swz128(row)) * 16;
-    bsrc[r] = reinterpret_cast<const char*>(B + (int64_t)epi.b_row(min(n0 + row, N - 1)) * ldb) + ch;
+    bsrc[r] = reinterpret_cast<const char*>(B + (int64_t)epi.b_row(min(n0 + row, N - 1)) * ldb) +
+              ch;
   }
   auto issue = [&](int i, int stage) {
     const int kt = wave + i * G::NW;
@@ -1021,7 +1024,8 @@ __global__ __launch_bounds__(G::NT) void gemm_skinny_kernel(const T* __restrict_
     for (int j = 0; j < G::TN; ++j)
 #pragma unroll
       for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<float4*>(mineC + (i * 32 + fr) * G::LDC + j * 32 + g * 8 + (lane >> 5) * 4) =
+        *reinterpret_cast<float4*>(mineC + (i * 32 + fr) * G::LDC + j * 32 + g * 8 +
+                                   (lane >> 5) * 4) =
             make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
                         acc[i][j][4 * g + 3]);
   __syncthreads();
@@ -1042,7 +1046,8 @@ __global__ __launch_bounds__(G::NT) void gemm_skinny_kernel(const T* __restrict_
 
 // Large grids: 256-row tiles on eight waves in two groups of four, one wave of
 // each group per SIMD, that take turns between a memory phase (LDS fragment
-// reads, DMA issue) and a matrix phase, half a phase pair apart: while one
+// reads, DMA issue) and a matrix phase, half a phase pair apart (the schedule
+// published as ping-pong, for warps and for the waves of a SIMD): while one
 // wave of a SIMD issues products, the other fills its registers, so neither
 // the LDS latency nor the DMA issue (a wave is held while the CU's address
 // unit is busy) leaves the matrix cores idle.  A slab takes two phase pairs
@@ -1050,11 +1055,11 @@ __global__ __launch_bounds__(G::NT) void gemm_skinny_kernel(const T* __restrict_
 // lower half (whose B fragments are still in registers).  The loop runs at the
 // card's power limit: 1.40 PFLOP/s by the slope over K at 4,096 x 4,096 with
 // this schedule and with all eight waves in phase alike, but this one also
-// holds it beside cold operands (31,503 x 1,024 x 5,120: 304 -> 285 us).  What
-// is left at K = 1,024 is the epilogue, 9 us of a 37 us GELU tile, in which
-// nothing overlaps (one workgroup per CU): so both staging passes' loads go out
-// at once when the loop ends (output add at 5,120 x 65,536: 826 -> 753 us) and
-// every wave takes part in both.  Writing from the accumulators without
+// holds it beside cold operands (31,503 x 1,024 x 5,120 in a call: 298 -> 269
+// us).  What is left at K = 1,024 is the epilogue, 9 us of a 37 us GELU tile, in
+// which nothing overlaps (one workgroup per CU): so both staging passes' loads
+// go out at once when the loop ends (output add at 5,120 x 65,536: 826 -> 753
+// us) and every wave takes part in both.  Writing from the accumulators without
 // staging, 16 bytes per lane and 32 per row, was slower (973 us).
 template <typename T, int TM_, int TN_, int WGM_, int WGN_>
 struct PhaseTile {
@@ -1151,7 +1156,8 @@ __global__ __launch_bounds__(G::NT) void gemm_phase_kernel(const T* __restrict__
     for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
       for (int i = 0; i < G::HTM; ++i)
-        af[ks][i] = *reinterpret_cast<const frag*>(as + i * 4096 + (((2 * ks + (lane >> 5)) ^ fsw) << 4));
+        af[ks][i] =
+            *reinterpret_cast<const frag*>(as + i * 4096 + (((2 * ks + (lane >> 5)) ^ fsw) << 4));
   };
   auto read_b = [&](int kt) {
     const char* bs = smem + (kt & 1) * G::STAGE_BYTES + (G::BM + wc * G::WN + fr) * 128;
@@ -1159,7 +1165,8 @@ __global__ __launch_bounds__(G::NT) void gemm_phase_kernel(const T* __restrict__
     for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
       for (int j = 0; j < G::TN; ++j)
-        bf[ks][j] = *reinterpret_cast<const frag*>(bs + j * 4096 + (((2 * ks + (lane >> 5)) ^ fsw) << 4));
+        bf[ks][j] =
+            *reinterpret_cast<const frag*>(bs + j * 4096 + (((2 * ks + (lane >> 5)) ^ fsw) << 4));
   };
   auto products = [&](auto half) {
     constexpr int I0 = decltype(half)::value * G::HTM;
@@ -1213,7 +1220,8 @@ __global__ __launch_bounds__(G::NT) void gemm_phase_kernel(const T* __restrict__
     // (A's lower half has landed)
     using WAIT_UP = std::integral_constant<int, LEFT >= 1 ? LOWER + UPPER : 0>;
     // (all of slab t + 1 but A's lower half)
-    using WAIT_LO = std::integral_constant<int, LEFT >= 2 ? G::A_OPS + LOWER : LEFT == 1 ? G::A_OPS : 0>;
+    using WAIT_LO =
+        std::integral_constant<int, LEFT >= 2 ? G::A_OPS + LOWER : LEFT == 1 ? G::A_OPS : 0>;
     read_a(t, 0);
     read_b(t);
     if constexpr (LEFT >= 1) {
@@ -1334,11 +1342,14 @@ static hipError_t launch_tiled(const T* A, int64_t lda, const T* B, int64_t ldb,
 //     -> 82.4; x 1,024: 23.0 and 23.4).
 // Larger bf16 grids take 256x256 tiles (PhaseTile) if those fill their rounds
 // well enough (round_fill, kWideGain): half the operand bytes per FLOP of a
-// 128x128 tile, one workgroup per CU with a two-slab ring of 64 KB slabs.  Otherwise 128x128 tiles of four waves (64x64 each) and a
-// two-slab ring (64 KB, two workgroups resident per CU hide each other's
-// latency).  Larger fp32 grids are bound by the matrix cores: 128x128 tiles if
-// their grid fills its rounds, else 64x128 (512 x 18,432 x 512: 103 and 89).
-// Epi::kWide is false for epilogues that launch() gives no 256x256 tile; Epi::kCols and min_cols() bound the tile's width from below.
+// 128x128 tile, one workgroup per CU with a two-slab ring of 64 KB slabs.
+// Otherwise 128x128 tiles of four waves (64x64 each) and a two-slab ring (64 KB,
+// two workgroups resident per CU hide each other's latency).  Larger fp32 grids
+// are bound by the matrix cores: 128x128 tiles if their grid fills its rounds,
+// else 64x128 (512 x 18,432 x 512: 103 and 89).
+// Epi::kWide is false for epilogues that launch() gives no 256x256 tile;
+// Epi::kCols and min_cols() bound the tile's width from below.
+//
 // Fraction of the workgroup slots busy over the rounds a grid of `tiles`
 // takes on `slots` resident workgroups.
 static inline double round_fill(int64_t tiles, int64_t slots) {
@@ -1353,7 +1364,8 @@ constexpr double kWideGain = 1.25;
 template <typename T, typename Epi, bool SPLIT = false>
 static hipError_t launch(const T* A, int64_t lda, const T* B, int64_t ldb, int M, int N, int K,
                          const Epi& epi, hipStream_t s, ASplit<T> sp = {}) {
-#define CR_TILED(...) return launch_tiled<T, __VA_ARGS__, Epi, SPLIT>(A, lda, B, ldb, M, N, K, epi, s, sp)
+#define CR_TILED(...) \
+  return launch_tiled<T, __VA_ARGS__, Epi, SPLIT>(A, lda, B, ldb, M, N, K, epi, s, sp)
   constexpr bool BF = sizeof(T) == 2;
   const int rows = epi.rows(M), mc = epi.min_cols();
   auto fits = [&](int bm, int bn) { return mc <= bn && grid_tiles(rows, N, bm, bn) <= 256; };

@@ -62,8 +62,9 @@ hipError_t gemm_bias_split(const T* A, int64_t lda, int K1, const T* A2, int64_t
 
 // QKV projection with the repair backbone's RoPE on Q and K (rotate-half
 // pairs, table rope[token][d_head/2] of (cos, sin)); Q is written scaled by
-// log2(e)/sqrt(d_head); K rows and V^T columns are written up to n_pad
-// (finite padding); V is written transposed, vt[head][d][n_pad].
+// log2(e)/sqrt(d_head); V is written transposed, vt[head][d][n_pad].  K rows and
+// V^T columns are written at least up to roundup(M, 64) (finite padding);
+// what lies beyond, up to n_pad, may stay unwritten.
 template <typename T>
 hipError_t gemm_qkv(const T* A, int64_t lda, const T* B, int M, int K, int d_b, int d_head,
                     T* q, T* k, T* vt, int64_t n_pad, const float* bias, const float2* rope,
@@ -87,7 +88,8 @@ hipError_t gemm_expand(const T* A, int64_t lda, const T* B, int M, int N, int K,
                        hipStream_t s);
 
 // ---- flash attention over per-row key intervals [lo, hi); q pre-scaled by
-// log2(e)/sqrt(d_head); k and vt padded to n_pad >= roundup(N, 64) keys.
+// log2(e)/sqrt(d_head); k and vt hold finite values up to key roundup(N, 64) <=
+// n_pad, and nothing beyond is read.
 // lo and hi must not decrease with the row (chunk_schedule's intervals, for
 // every topology, satisfy this): the kernel reads a tile's key range from
 // its first and last rows.  max_keys: keys of the longest row (it only picks

@@ -206,12 +206,13 @@ hipError_t compress_segments(const T* kv, KvStrides ks, int n_layers, const T* w
   if (N <= 0) return hipSuccess;
   const int S = 2 * n_layers * ks.n_kv_heads;
   // 16-token blocks per wave: four once the grid still has two workgroups per
-  // CU, two once it has one, as long as the registers last (fp32: two, heads
-  // of at most 128); else one.  More blocks keep more cache reads in flight per
-  // wave and use each weight fragment more often, but leave CUs idle in a small
-  // grid (144 segments of 128; us on 1, 2 and 4 blocks: 57 tokens 4.0, 4.5,
-  // 5.8; 512 tokens 10.5, 9.4, 10.1; 1,177 tokens 19.9, 16.9, 15.2; 512
-  // segments, 200 tokens 14.4, 13.2, 11.2; fp32, 512 tokens 22.3 and 21.0).
+  // CU, two once it has about one, as long as the registers last (fp32: two,
+  // heads of at most 128); else one.  More blocks keep more cache reads in
+  // flight per wave and use each weight fragment more often, but leave CUs idle
+  // in a small grid (144 segments of 128; us on 1, 2 and 4 blocks: 57 tokens 4.1,
+  // 4.5, 5.8; 224 tokens, 252 workgroups of two, 5.2, 4.8, 5.8; 512 tokens 9.0,
+  // 8.2, 9.2; 1,177 tokens 17.1, 14.0, 12.1; 512 segments, 200 tokens 13.4, 11.8,
+  // 10.6; fp32, 256 tokens 13.2 and 14.3, 512 19.8 and 19.1).
   auto grid = [&](int tb) { return (int64_t)((N + 16 * tb - 1) / (16 * tb)) * ((S + 3) / 4); };
   const bool four = sizeof(T) == 2 && grid(4) >= 512;
   const bool two = (sizeof(T) == 2 || ks.head_dim <= 128) && grid(2) >= 250;
