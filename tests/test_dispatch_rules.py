@@ -62,7 +62,8 @@ def test_output_add_takes_the_faster_tiles(rules, M, N, K, small, wide):
 
 
 MB = 1 << 20
-# attention workgroups, their queries, bytes to prefetch, bytes of the repairer: us of the call without, with
+# attention workgroups, their queries, bytes to prefetch, bytes of the repairer:
+# us of the call without, with
 PREFETCH = [
     (32, 32, 26 * MB, 267 * MB, 384.6, 347.2), (144, 32, 26 * MB, 267 * MB, 481.6, 488.1),
     (128, 32, 26 * MB, 267 * MB, 444.8, 419.8), (192, 32, 26 * MB, 267 * MB, 510.5, 494.3),

@@ -80,10 +80,10 @@ SMALL = [
          d_b=128, n_heads=2, d_seg=8, n_blocks=0),
     dict(lengths=((40, 97),), dtype="f32", L=2, H=1, dh=64, E=64, d_c=64, d_b=128,
          n_heads=4, d_seg=8, n_blocks=0),
-    # 1,177 ragged tokens with 16 and 32 heads: at least 128 query tiles x
-    # heads, so the attention takes its 128-query tiles (64- and 32-wide
-    # heads, last tile ragged) while the 1,024-column GEMMs still take the
-    # 64x64 tiles of short batches and FFN1 the 128-row ones
+    # 1,177 ragged tokens: 16 heads of 64 on 64-query attention tiles (160
+    # workgroups of 128 queries would leave CUs idle) and 32 heads of 32 on
+    # 128-query ones (320), last tile ragged; the 1,024-column GEMMs take
+    # 128x64 tiles and FFN1 192x128 ones
     dict(lengths=((300, 1, 517), (260, 99)), dtype="bf16", L=2, H=2, dh=64, E=128, d_c=64,
          d_b=1024, n_heads=16, d_seg=8),
     dict(lengths=((300, 1, 517), (260, 99)), dtype="bf16", L=1, H=2, dh=64, E=128, d_c=64,
@@ -130,7 +130,7 @@ def test_parity_at_tile_boundaries(n, dtype):
     # d_b = 1024: FFN1 and QKV on one round of 256x256 and 256x192 tiles, the
     # last tile rows ragged
     (3900, dict()),
-    # 1,024-column products on 192x128 tiles; QKV on 128x128 ones
+    # 1,024-column products on 192x128 tiles; QKV on 204 tiles of 256x256
     (4300, dict()),
     # QKV on 256x256 tiles in the weights' column order
     (4800, dict()),
@@ -159,6 +159,12 @@ def test_parity_on_large_tiles(n, cfg):
     (500, 160, "f32"),     # (one: the registers do not last for two)
     (1950, 96, "bf16"),    # four
     (200, 128, "bf16"),    # one
+    # the other head sizes, in the forms that no other case runs
+    (500, 32, "bf16"), (1950, 32, "bf16"), (1950, 64, "bf16"), (200, 160, "bf16"),
+    (500, 160, "bf16"), (1950, 160, "bf16"), (200, 192, "bf16"), (500, 192, "bf16"),
+    (1950, 192, "bf16"), (500, 224, "bf16"), (1950, 224, "bf16"), (500, 256, "bf16"),
+    (1950, 256, "bf16"), (500, 32, "f32"), (500, 64, "f32"), (500, 96, "f32"), (200, 128, "f32"),
+    (200, 192, "f32"), (200, 224, "f32"), (200, 256, "f32"),
 ])
 def test_compression_token_blocks(n, dh, dtype):
     """Token blocks per wave of the segment projections, with a last segment
@@ -169,12 +175,68 @@ def test_compression_token_blocks(n, dh, dtype):
     assert_parity(gpu_repair(inp), oracle_repair(inp), W.kv_layer_major_to_canonical(inp.kv), w)
 
 
+@pytest.mark.parametrize("n,placed,cfg", [
+    # QKV on 192x128 tiles (288 tiles of 128x128 would take two rounds)
+    (1500, False, dict(dtype="bf16", d_b=1024, n_heads=16)),
+    # the output add of a 36-layer cache on 192x128 tiles
+    (150, False, dict(dtype="bf16", L=36, dh=128)),
+    (150, True, dict(dtype="bf16", L=36, dh=128)),
+    # fp32: the output add on 64x128 tiles and, from 772 tokens, on 128x128 ones
+    # of four waves, plain and rotating
+    (200, False, dict(dtype="f32", L=36, dh=128)),
+    (200, True, dict(dtype="f32", L=36, dh=128)),
+    (800, False, dict(dtype="f32", L=36, dh=128)),
+    (800, True, dict(dtype="f32", L=36, dh=128)),
+    # fp32, 128x128 tiles of eight waves (one to a CU): FFN1 and a 4,096-column
+    # output add, plain and rotating; QKV
+    (1000, False, dict(dtype="f32", L=8, dh=128, d_b=1024, n_heads=16)),
+    (1000, True, dict(dtype="f32", L=8, dh=128, d_b=1024, n_heads=16)),
+    (1200, False, dict(dtype="f32", d_b=1024, n_heads=16)),
+    # ... of four waves: FFN1; QKV
+    (2000, False, dict(dtype="f32", d_b=1024, n_heads=16)),
+    (2500, False, dict(dtype="f32", d_b=1024, n_heads=16)),
+    # ... the fusion's split K, and 128-query attention tiles over 64-wide heads
+    (2000, False, dict(dtype="f32", d_b=2048, n_heads=32, ffn_mult=1)),
+    # K = 2,048: QKV and the output add, plain and rotating, on 128x128 tiles of
+    # two K groups, and the plain one on 256x128
+    (400, False, dict(dtype="bf16", d_b=2048, n_heads=32)),
+    (100, False, dict(dtype="bf16", L=36, dh=128, d_b=2048, n_heads=32)),
+    (100, True, dict(dtype="bf16", L=36, dh=128, d_b=2048, n_heads=32)),
+    (200, False, dict(dtype="bf16", L=36, dh=128, d_b=2048, n_heads=32)),
+    # the rotating output add on 128x64 tiles (64-wide heads)
+    (400, True, dict(dtype="bf16", L=16)),
+])
+def test_parity_on_tiles_between(n, placed, cfg):
+    """Tiles that ordinary calls take between the sizes above: grids just over
+    one round of 128x128 tiles, and fp32 products too large for 64x64 ones."""
+    from helpers import oracle_kwargs
+    from paper_2609_35139_amd import binding as B
+    base = dict(L=1, H=2, dh=64, E=64, d_c=64, d_b=128, n_heads=2, d_seg=8, n_blocks=1, ffn_mult=4)
+    w = small_workload(((n // 3, n - n // 3 - 6), (6,)), seed=29, **{**base, **cfg})
+    inp = W.make_inputs(w)
+    opts = dict(global_rope=dict(theta=1e4), position_offset=[7, 0]) if placed else {}
+    Y = gpu_repair(inp, options=B.Options(**opts) if placed else None)
+    assert_parity(Y, oracle_repair(inp, **oracle_kwargs(w, **opts)),
+                  W.kv_layer_major_to_canonical(inp.kv), w)
+
+
 def test_two_slab_product_on_256_row_tiles():
     """FFN1 of d_b = 128 and 2,048 columns: K is two slabs of the two-phase
     kernel (its peeled loop ends alone), 256 tiles, the last row of them ragged."""
     w = small_workload(((500, 1, 300), (511,)) * 6 + ((127,),), seed=31, dtype="bf16", L=1, H=1,
                        dh=64, E=64, d_c=64, d_b=128, n_heads=2, d_seg=8, n_blocks=1, ffn_mult=16)
     assert 7936 < w.n_tokens < 8192
+    inp = W.make_inputs(w)
+    assert_parity(gpu_repair(inp), oracle_repair(inp), W.kv_layer_major_to_canonical(inp.kv), w)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_split_product_on_four_wave_tiles(dtype):
+    """The fusion and FFN2 (A split along K) of d_b = 384 on 471 tiles of
+    128x128, two to a CU: 256-column tiles would be half padding."""
+    w = small_workload(((250, 1, 249),) * 39 + ((499,),), seed=37, dtype=dtype, L=1, H=1, dh=32,
+                       E=64, d_c=64, d_b=384, n_heads=6, d_seg=8, n_blocks=2, ffn_mult=1)
+    assert 156 * 128 < w.n_tokens <= 157 * 128
     inp = W.make_inputs(w)
     assert_parity(gpu_repair(inp), oracle_repair(inp), W.kv_layer_major_to_canonical(inp.kv), w)
 

@@ -228,11 +228,10 @@ def test_global_placement_at_the_4x256_workload():
     assert_parity(Y, Yr, X, w)
 
 
-# 1,177 ragged tokens in 16 heads of 64: at least 128 query tiles x heads, so
-# the attention takes its 128-query tiles (the small cases above and the
-# 4 x 256 workload take the 64-query tiles of short batches)
+# 1,177 ragged tokens in 32 heads of 64: 320 workgroups of 128 queries, more
+# than the 256 below which the attention takes shorter query tiles
 WIDE = dict(lengths=((300, 1, 517), (260, 99)), dtype="bf16", L=2, H=2, dh=64, E=128, d_c=64,
-            d_b=1024, n_heads=16, d_seg=8)
+            d_b=2048, n_heads=32, d_seg=8)
 
 
 @pytest.mark.parametrize("name", ["token_causal", "bidirectional", "block_diagonal"])
@@ -260,6 +259,7 @@ def test_global_placement_on_128_query_tiles():
     (513, 16, 1024, "bf16"),     # one more: 64-query tiles
     (2048, 16, 1024, "bf16"),    # 512 of them, rows of over 512 keys but under block_diagonal
     (700, 32, 2048, "bf16"),     # 352 would be needed, rows of at most 353 keys: 128-query tiles
+    (600, 32, 1024, "bf16"),     # 320 of 64-query tiles, two to a CU (32-wide heads)
     (1177, 32, 2048, "bf16"),    # 320 of 128-query tiles, 64-wide heads
     (1177, 32, 1024, "bf16"),    # the same, 32-wide heads
     (701, 8, 512, "f32"),        # 32-query tiles and 32-key tiles
