@@ -1337,7 +1337,9 @@ static hipError_t launch_tiled(const T* A, int64_t lda, const T* B, int64_t ldb,
 //     waves, which read a third fewer fragment bytes per product (+3-4%).
 //   192x128 (bf16): eight waves of 96x32 (5,120 x 1,024 x 5,120: 74.7 -> 59.9
 //     against 128x128 tiles in two rounds, x 1,024: 19.1 -> 17.0; 1,177 x
-//     4,096 x 1,024: 19.7 -> 16.5);
+//     4,096 x 1,024: 19.7 -> 16.5; the output add of 18,432 columns, 135 and 191
+//     rows: K = 512 13.2 -> 10.7 and 13.7 -> 11.9, 1,024 21.0 -> 16.5 and 21.9 ->
+//     18.3);
 //   256x128 (bf16): two K groups, from K = 2048 (8,192 x 1,024 x 5,120: 95.1
 //     -> 82.4; x 1,024: 23.0 and 23.4).
 // Larger bf16 grids take 256x256 tiles (PhaseTile) if those fill their rounds
