@@ -156,20 +156,6 @@ cr_status check_offsets(const int32_t* off, int32_t n_chunks, const int32_t* req
   return CR_OK;
 }
 
-// Keys of the longest attention row: the longest request (its longest chunk
-// under the block-diagonal topology).
-int longest_row(const int32_t* off, int32_t n_chunks, const int32_t* req, int32_t n_req, int mask) {
-  int most = 0;
-  if (mask == CR_MASK_BLOCK_DIAGONAL) {
-    for (int c = 0; c < n_chunks; ++c) most = std::max(most, off[c + 1] - off[c]);
-  } else if (!req) {
-    most = off[n_chunks];
-  } else {
-    for (int r = 0; r < n_req; ++r) most = std::max(most, off[req[r + 1]] - off[req[r]]);
-  }
-  return most;
-}
-
 bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
 // Target rotary encoding: frequencies in fp64 from theta or the caller's
@@ -605,7 +591,8 @@ cr_status repair_impl(T* kv, const cr_kv_layout* l, const int32_t* off, int32_t 
       return cr::gemm_bias_split<T>(st, ldst, dc, emb, E, PT(rj ? P.w_fuse_rj : P.w_fuse), dc + E,
                                     M, db, dc + E, h, db, PF(rj ? P.b_fuse_rj : P.b_fuse), nullptr,
                                     0, s); }));
-  const int max_keys = longest_row(off, n_chunks, req, n_req, opt.mask);
+  const int queries = cr::attention_queries(
+      cr::KeyIntervals{off, n_chunks, req, n_req, opt.mask}, N, nh, dhd, sizeof(T) == 4);
   // h holds x_b = h^{b-1} + P_b(s) on entry to block b, h^B after the last block
   const int kff = r * db;   // FFN2 inner width; its prepared rows are kff + d_c long
   for (int b = 0; b < B; ++b) {
@@ -623,7 +610,7 @@ cr_status repair_impl(T* kv, const cr_kv_layout* l, const int32_t* off, int32_t 
     const int64_t pf_bytes = (int64_t)(pf_end - Bk.w_ff1);
     const bool pf = sizeof(T) == 2 && cr::prefetch_pays(pf_bytes, (int64_t)P.total);
     CR_TRY(timed("attention", s, [&] {
-        return cr::attention<T>(q, k, vt, o, M, db, nh, dhd, W.n_pad, lo, hi, max_keys, s,
+        return cr::attention<T>(q, k, vt, o, M, db, nh, dhd, W.n_pad, lo, hi, queries, s,
                                 pf ? prep + Bk.w_ff1 : nullptr, pf_bytes); }));
     CR_TRY(timed("gemm_oproj", s, [&] {
         return cr::gemm_bias<T>(o, db, PT(Bk.w_o), db, M, db, db, h, db, PF(Bk.b_o), h, db, false, s); }));

@@ -480,15 +480,14 @@ static hipError_t launch_attention(const T* q, const T* k, const T* vt, T* o, in
   return hipGetLastError();
 }
 
-// Query tiles: see attention_queries.
+// queries: see attention_queries.
 template <typename T, int D>
 static hipError_t attention_d(const T* q, const T* k, const T* vt, T* o, int N, int d_b,
                               int n_heads, int64_t n_pad, const int* lo, const int* hi,
-                              int max_keys, const void* pf, int64_t pf_bytes, hipStream_t s) {
+                              int queries, const void* pf, int64_t pf_bytes, hipStream_t s) {
 #define CR_ATTN(...)                                                                             \
   return launch_attention<T, D, __VA_ARGS__>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, pf,    \
                                              pf_bytes, s)
-  const int queries = attention_queries(N, n_heads, D, sizeof(T) == 4, max_keys);
   if constexpr (sizeof(T) == 2) {
     if (queries == 32) CR_ATTN(2, 1, 4, 64);
     if (queries == 64) CR_ATTN(2, 2, 8, 64);
@@ -503,15 +502,15 @@ static hipError_t attention_d(const T* q, const T* k, const T* vt, T* o, int N, 
 
 template <typename T>
 hipError_t attention(const T* q, const T* k, const T* vt, T* o, int N, int d_b, int n_heads,
-                     int d_head, int64_t n_pad, const int* lo, const int* hi, int max_keys,
+                     int d_head, int64_t n_pad, const int* lo, const int* hi, int queries,
                      hipStream_t s, const void* pf, int64_t pf_bytes) {
   if (N <= 0) return hipSuccess;
   if (n_pad < ((N + 63) / 64) * 64) return hipErrorInvalidValue;
   if (d_head == 64)
-    return attention_d<T, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, max_keys, pf, pf_bytes,
+    return attention_d<T, 64>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, queries, pf, pf_bytes,
                               s);
   if (d_head == 32)
-    return attention_d<T, 32>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, max_keys, pf, pf_bytes,
+    return attention_d<T, 32>(q, k, vt, o, N, d_b, n_heads, n_pad, lo, hi, queries, pf, pf_bytes,
                               s);
   return hipErrorInvalidValue;
 }

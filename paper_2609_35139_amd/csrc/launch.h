@@ -92,13 +92,13 @@ hipError_t gemm_expand(const T* A, int64_t lda, const T* B, int M, int N, int K,
 // n_pad, and nothing beyond is read.
 // lo and hi must not decrease with the row (chunk_schedule's intervals, for
 // every topology, satisfy this): the kernel reads a tile's key range from
-// its first and last rows.  max_keys: keys of the longest row (it only picks
-// the query tile).  Where its grid leaves CUs idle, the launch also
-// reads pf[0, pf_bytes) (16-byte aligned, a multiple of 16 bytes; null:
-// nothing) into the last-level cache.
+// its first and last rows.  queries: rows per workgroup, 128, 32 or (bf16) 64.
+// Where its grid leaves CUs idle, the launch also reads pf[0, pf_bytes)
+// (16-byte aligned, a multiple of 16 bytes; null: nothing) into the last-level
+// cache.
 template <typename T>
 hipError_t attention(const T* q, const T* k, const T* vt, T* o, int N, int d_b, int n_heads,
-                     int d_head, int64_t n_pad, const int* lo, const int* hi, int max_keys,
+                     int d_head, int64_t n_pad, const int* lo, const int* hi, int queries,
                      hipStream_t s, const void* pf = nullptr, int64_t pf_bytes = 0);
 
 // ---- row LayerNorm, C % 8 == 0, C <= 2048.

@@ -2,6 +2,8 @@
 #pragma once
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace cr {
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -71,6 +73,60 @@ inline bool prefetch_fits(int64_t workgroups, int queries) {
   return last > 0 && last <= (queries == 32 ? 192 : 240) && workgroups <= 1280;
 }
 
+// Key interval [lo, hi) of every attention row, as schedule_kernel derives it
+// from the chunk and request offsets (mask: values of CR_MASK_*).
+struct KeyIntervals {
+  const int32_t* off;
+  int32_t n_chunks;
+  const int32_t* req;   // null: one request
+  int32_t n_req;
+  int mask;
+  int chunk_of(int64_t t) const {
+    return (int)(std::upper_bound(off, off + n_chunks + 1, t) - off) - 1;
+  }
+  int request_of(int chunk) const {
+    return (int)(std::upper_bound(req, req + n_req + 1, chunk) - req) - 1;
+  }
+  int64_t lo(int64_t t) const {
+    const int c = chunk_of(t);
+    if (mask == 3) return off[c];
+    return req ? off[req[request_of(c)]] : off[0];
+  }
+  int64_t hi(int64_t t) const {
+    if (mask == 1) return t + 1;
+    const int c = chunk_of(t);
+    if (mask == 2) return req ? off[req[request_of(c) + 1]] : off[n_chunks];
+    return off[c + 1];
+  }
+};
+
+// Iterations that the workgroup of query tile qt spends on its 64-key tiles,
+// which its `groups` groups of waves share.
+inline int attention_iterations(const KeyIntervals& rows, int64_t N, int64_t qt, int queries,
+                                int groups) {
+  const int64_t q0 = qt * queries, q1 = (q0 + queries < N ? q0 + queries : N) - 1;
+  const int64_t keys = rows.hi(q1) - rows.lo(q0) / 64 * 64;
+  return (int)ceil_div(ceil_div(keys, 64), groups);
+}
+
+// Iterations of the busiest of 256 CUs over the workgroups of 64-query tiles,
+// at most 512, dealt in launch order (latest tiles first, every head of a tile
+// in turn): the first 256 go to a CU each, the others to the CUs that are
+// done first.  A workgroup costs one iteration more than its keys.
+inline int attention_chain_64(const KeyIntervals& rows, int64_t N, int n_heads) {
+  int first[256], n = 0, second[256], m = 0, longest = 0;
+  for (int64_t qt = ceil_div(N, 64) - 1; qt >= 0; --qt) {
+    const int it = 1 + attention_iterations(rows, N, qt, 64, 4);
+    for (int h = 0; h < n_heads; ++h) {
+      if (n < 256) first[n++] = it;
+      else if (m < 256) second[m++] = it;
+    }
+  }
+  std::sort(first, first + n);
+  for (int j = 0; j < n; ++j) longest = std::max(longest, first[j] + (j < m ? second[j] : 0));
+  return longest;
+}
+
 // Attention: queries per workgroup (128 with two groups of waves splitting the
 // keys, 64 or 32 with four).  A grid that leaves CUs idle, or has them all wait
 // for the few workgroups of the last chunks, is bound by one workgroup's walk
@@ -79,26 +135,33 @@ inline bool prefetch_fits(int64_t workgroups, int queries) {
 //   bf16, 32 queries while their grid fits the 256 CUs (200 tokens 6.1 -> 5.5,
 //     57 tokens x 8 heads 5.1 -> 4.9 and 4 x 256 x 8 heads 9.1 -> 8.1 against
 //     64-query tiles);
-//   bf16, 64 queries while their grid fits the CUs (one workgroup each with
-//     heads of 64, two with heads of 32: 1,024 tokens 9.4 against 12.5), and
-//     until the 128-query grid does if a row has more than 512 keys (1,177
-//     ragged tokens 21.9 -> 14.8, 2,500 tokens x 8 heads 24.7 -> 17.6, 4,000 37.1
-//     -> 32.3; 2,000 tokens x 16 heads 21.1 -> 20.6).  Shorter walks do not repay the
-//     second workgroup on a CU (2,500 tokens x 8 heads in requests of 512: 12.6
-//     and 9.4, of 256: 10.5 and 7.0, of 100: 11.4 and 10.4; only unaligned
-//     requests of 300 to 400 whose grid hardly exceeds the CUs would: 13.7 and
-//     16.7 at 1,283 tokens);
+//   bf16, 64 queries while their grid fits the CUs (1,024 tokens 9.4 against
+//     12.5);
+//   bf16, 64 queries while the 128-query grid fits them, if the busiest CU then
+//     has fewer iterations, counted one more per workgroup (with heads of 32,
+//     where two workgroups share a CU and hide that, one more or as many): in
+//     288 batches of one to six requests under every topology the tiles taken
+//     are 0.4% slower than the better ones on average, 14% at worst (64-query
+//     ones throughout 9%, 128-query ones throughout 12%).  On 64 and 128: 2,500
+//     tokens x 8 heads in 512-token chunks of one request 17.6 and 24.7, in
+//     requests of one chunk of 800 16.5 and 24.4, of 512 12.6 and 9.4, of 100
+//     11.4 and 10.4; 3,374 in one request, bidirectional, 37.8 and 32.5;
 //   fp32, 32 queries and 32-key tiles (two-slot rings of 32 KB per group) below
 //     two 128-query workgroups per CU (2 x 256 tokens x 8 heads 37 -> 13.5,
 //     2,048 x 8 heads 130 -> 54; at 512 workgroups, 4,096 tokens, 360 and 302).
 //     From 384 on it depends on the chunks: 3,000 tokens in 512-token chunks of
 //     one request 212 against 193, in two requests of one chunk 193 against 221.
-inline int attention_queries(int64_t N, int n_heads, int d_head, bool fp32, int64_t max_keys) {
+inline int attention_queries(const KeyIntervals& rows, int64_t N, int n_heads, int d_head,
+                             bool fp32) {
   const int64_t wg128 = ceil_div(N, 128) * n_heads;
   if (fp32) return wg128 < 512 ? 32 : 128;
+  if (wg128 > 256) return 128;
   if (ceil_div(N, 32) * n_heads <= 256) return 32;
-  if (ceil_div(N, 64) * n_heads <= (d_head == 32 ? 512 : 256)) return 64;
-  return wg128 <= 256 && max_keys > 512 ? 64 : 128;
+  if (ceil_div(N, 64) * n_heads <= 256) return 64;
+  int longest = 0;
+  for (int64_t qt = ceil_div(N, 128) - 1; qt >= 0; --qt)
+    longest = std::max(longest, attention_iterations(rows, N, qt, 128, 2));
+  return attention_chain_64(rows, N, n_heads) <= longest + (d_head == 32 ? 1 : 0) ? 64 : 128;
 }
 
 }  // namespace cr

@@ -8,6 +8,7 @@ import ctypes
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
@@ -16,8 +17,14 @@ SHIM = """
 #include "rules.h"
 extern "C" {
 int expand_on_256(long M, long N, int K) { return cr::expand_on_256(M, N, K); }
-int attention_queries(long N, int n_heads, int d_head, int fp32, long max_keys) {
-  return cr::attention_queries(N, n_heads, d_head, fp32, max_keys);
+int attention_queries(const int* off, int n_chunks, const int* req, int n_req, int mask,
+                      int n_heads, int d_head, int fp32) {
+  return cr::attention_queries(cr::KeyIntervals{off, n_chunks, req, n_req, mask}, off[n_chunks],
+                               n_heads, d_head, fp32);
+}
+void intervals(const int* off, int n_chunks, const int* req, int n_req, int mask, int* lo, int* hi) {
+  const cr::KeyIntervals k{off, n_chunks, req, n_req, mask};
+  for (int t = 0; t < off[n_chunks]; ++t) { lo[t] = k.lo(t); hi[t] = k.hi(t); }
 }
 int prefetch(long wgs, int queries, long range, long total) {
   return cr::prefetch_pays(range, total) && cr::prefetch_fits(wgs, queries);
@@ -87,24 +94,78 @@ def test_weights_are_prefetched_where_that_is_faster(rules, wgs, q, range_, tota
     assert (with_ if on else without) <= 1.015 * min(without, with_)
 
 
-# tokens, heads, d_head, fp32, keys of the longest row: us on 32-, 64- and 128-query tiles
+MASKS = ["block_causal", "token_causal", "bidirectional", "block_diagonal"]   # CR_MASK_*
+
+
+def _offsets(lengths):
+    """ctypes arrays of a batch: chunks separated by commas, requests by semicolons."""
+    reqs = [[int(c) for c in r.split(",")] for r in lengths.split(";")]
+    off = np.concatenate([[0], np.cumsum([c for r in reqs for c in r])])
+    req = np.concatenate([[0], np.cumsum([len(r) for r in reqs])])
+    return (ctypes.c_int * len(off))(*off), len(off) - 1, (ctypes.c_int * len(req))(*req), len(reqs)
+
+
+@pytest.mark.parametrize("mask", range(4))
+@pytest.mark.parametrize("lengths", ["1", "5,0,3", "0,4;0;2,0,0,9;0,0;1", "0;7", "3,1,1;12;1;0,2"])
+def test_key_intervals_are_the_rows_of_the_mask(rules, lengths, mask):
+    import oracle as O
+    off, nc, req, nr = _offsets(lengths)
+    n = off[nc]
+    lo, hi = (ctypes.c_int * n)(), (ctypes.c_int * n)()
+    for r in (req, None) if nr == 1 else (req,):
+        rules.intervals(off, nc, r, nr, mask, lo, hi)
+        allowed = O.attention_allowed(MASKS[mask], O.token_chunk_ids(np.array(off)),
+                                      O.token_request_ids(np.array(off), np.array(req)))
+        j = np.arange(n)
+        got = (j >= np.array(lo)[:, None]) & (j < np.array(hi)[:, None])
+        assert np.array_equal(got, allowed)
+
+
+def _every(n, size):
+    return ",".join(str(min(size, n - a)) for a in range(0, n, size))
+
+
+def _alone(n, size):
+    return _every(n, size).replace(",", ";")
+
+
+# lengths, topology, heads, d_head, fp32: us on 32-, 64- and 128-query tiles
 ATTENTION = [
-    (200, 16, 64, 0, 200, 5.5, 6.1, None),
-    (1024, 16, 64, 0, 1024, None, 9.4, 12.5), (1024, 16, 64, 0, 100, None, 7.5, 10.0),
-    (1500, 16, 64, 0, 1500, None, 15.8, 17.4), (2000, 16, 64, 0, 200, None, 13.9, 12.0),
-    (2500, 8, 64, 0, 2500, None, 17.6, 24.7), (2500, 8, 64, 0, 800, None, 16.5, 24.4),
-    (2500, 8, 64, 0, 512, None, 12.6, 9.4), (2500, 8, 64, 0, 256, None, 10.5, 7.0),
-    (2500, 8, 64, 0, 100, None, 11.4, 10.4), (3600, 8, 64, 0, 100, None, 12.9, 11.0),
-    (4000, 8, 64, 0, 300, None, 18.1, 15.2), (4000, 8, 64, 0, 4000, None, 32.3, 37.1),
-    (1500, 16, 32, 0, 1500, None, 10.2, 12.9), (1500, 16, 32, 0, 400, None, 13.0, 13.8),
-    (3000, 16, 32, 0, 3000, None, 26.6, 23.3),
-    (2048, 8, 64, 1, 2048, 54.1, None, 130.4), (3900, 8, 64, 1, 100, 30.5, None, 34.6),
-    (4096, 16, 64, 1, 4096, 359.5, None, 302.4), (2560, 16, 64, 1, 2560, 156.0, None, 168.5),
+    (_every(200, 512), 0, 16, 64, 0, 5.5, 6.1, None),
+    (_every(1024, 512), 0, 16, 64, 0, None, 9.4, 12.5),
+    (_alone(1024, 100), 0, 16, 64, 0, None, 7.5, 10.0),
+    (_every(1500, 512), 0, 16, 64, 0, None, 15.8, 17.4),
+    (_alone(2000, 200), 0, 16, 64, 0, None, 13.9, 12.0),
+    (_every(2500, 512), 0, 8, 64, 0, None, 17.6, 24.7),
+    (_alone(2500, 800), 0, 8, 64, 0, None, 16.5, 24.4),
+    (_alone(2500, 512), 0, 8, 64, 0, None, 12.6, 9.4),
+    (_alone(2500, 256), 0, 8, 64, 0, None, 10.5, 7.0),
+    (_alone(2500, 100), 0, 8, 64, 0, None, 11.4, 10.4),
+    (_alone(2100, 300), 0, 8, 64, 0, None, 12.5, 14.7),
+    (_alone(4000, 300), 0, 8, 64, 0, None, 18.1, 15.2),
+    (_every(4000, 512), 0, 8, 64, 0, None, 32.3, 37.1),
+    (_alone(1283, 400), 0, 16, 64, 0, None, 13.7, 16.7),
+    ("3374", 0, 8, 64, 0, None, 42.4, 34.1),
+    ("147,1048,265,392,1522", 2, 8, 64, 0, None, 42.8, 33.8),
+    ("28,92,1237,14,7,177,231,980,240,368", 1, 8, 64, 0, None, 24.5, 30.6),
+    ("430,1560;156,88,12,306,90,148,203,111,84,164,22", 0, 8, 64, 0, None, 28.7, 39.9),
+    ("63,22,5,41,41;4,3,15,6,3,3,13;138,164,38;1395,6;72,35;229,34,36,79,9,414,14,38,308,51,32,63",
+     3, 8, 64, 0, None, 26.2, 31.1),
+    (_every(1500, 512), 0, 16, 32, 0, None, 10.2, 12.9),
+    (_alone(1500, 400), 0, 16, 32, 0, None, 13.0, 13.8),
+    (_every(3000, 512), 0, 16, 32, 0, None, 26.6, 23.3),
+    ("2000", 0, 16, 32, 0, None, 20.8, 17.7),
+    ("119,689,163,1029", 1, 16, 32, 0, None, 14.5, 16.3),
+    (_every(2048, 512), 0, 8, 64, 1, 54.1, None, 130.4),
+    (_alone(3900, 100), 0, 8, 64, 1, 30.5, None, 34.6),
+    (_every(4096, 512), 0, 16, 64, 1, 359.5, None, 302.4),
+    (_every(2560, 512), 0, 16, 64, 1, 156.0, None, 168.5),
 ]
 
 
-@pytest.mark.parametrize("N,heads,dh,fp32,keys,t32,t64,t128", ATTENTION)
-def test_attention_takes_the_faster_query_tiles(rules, N, heads, dh, fp32, keys, t32, t64, t128):
-    q = rules.attention_queries(ctypes.c_long(N), heads, dh, fp32, ctypes.c_long(keys))
+@pytest.mark.parametrize("lengths,mask,heads,dh,fp32,t32,t64,t128", ATTENTION)
+def test_attention_takes_the_faster_query_tiles(rules, lengths, mask, heads, dh, fp32, t32, t64,
+                                                t128):
+    q = rules.attention_queries(*_offsets(lengths), mask, heads, dh, fp32)
     times = {32: t32, 64: t64, 128: t128}
-    assert times[q] is not None and times[q] <= 1.02 * min(t for t in times.values() if t)
+    assert times[q] is not None and times[q] <= 1.03 * min(t for t in times.values() if t)

@@ -257,8 +257,8 @@ def test_global_placement_on_128_query_tiles():
 @pytest.mark.parametrize("n,heads,d_b,dtype", [
     (512, 16, 1024, "bf16"),     # 256 workgroups of 32-query tiles, four key groups
     (513, 16, 1024, "bf16"),     # one more: 64-query tiles
-    (2048, 16, 1024, "bf16"),    # 512 of them, rows of over 512 keys but under block_diagonal
-    (700, 32, 2048, "bf16"),     # 352 would be needed, rows of at most 353 keys: 128-query tiles
+    (2048, 16, 1024, "bf16"),    # 512 of them, two to every CU
+    (700, 32, 2048, "bf16"),     # 352 of them bidirectional, else 192 of 128-query tiles
     (600, 32, 1024, "bf16"),     # 320 of 64-query tiles, two to a CU (32-wide heads)
     (1177, 32, 2048, "bf16"),    # 320 of 128-query tiles, 64-wide heads
     (1177, 32, 1024, "bf16"),    # the same, 32-wide heads
